@@ -70,6 +70,9 @@ struct nbt_ig_ctx {
     nbt::TrajBox* boxes = nullptr;
     size_t boxes_bytes = 0;
     bool boxes_async = false;
+    // scratch of split trajectory calls: bitsets and per-trajectory slots, of one fixed size
+    uint32_t* traj_bits = nullptr;
+    nbt::TrajAccum* traj_acc = nullptr;
     unsigned long long* topk_keep = nullptr;   // top-k selection scratch
     size_t topk_bytes = 0;
     bool topk_async = false;

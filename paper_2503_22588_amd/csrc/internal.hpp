@@ -101,6 +101,30 @@ struct TrajBox {
     uint32_t pad;
 };
 
+// Scratch of trajectories whose rays are split over several workgroups: a
+// bitset region per trajectory (kTrajSplitWords words dealt evenly) and this
+// slot, both cleared by the box pre-pass of every call.
+constexpr uint32_t kTrajSplitMost = 2048;            // trajectories of a split call
+constexpr uint32_t kTrajSplitWords = 32u << 20;      // bitset words of all of them (128 MiB)
+constexpr uint32_t kTrajSplitCap = 1u << 16;         // bitset words of one of them at most
+constexpr int kTrajParts = 64;                       // workgroups that sum up one trajectory at most
+struct TrajAccum {
+    unsigned long long visits;
+    unsigned int invalid, count;                     // count: parts that have written theirs
+    unsigned long long gain[kTrajParts];             // binary64 bits
+    unsigned long long occ_free[kTrajParts];         // occupied | free << 32
+    unsigned long long unknown[kTrajParts];
+};
+
+// How a call of T trajectories is split; groups == 1: one workgroup each.
+struct TrajSplit {
+    uint32_t groups;         // workgroups that share one trajectory's rays
+    uint32_t parts;          // workgroups that sum up its bitset
+    uint32_t cap_words;      // bitset words per trajectory; a larger box is left to one workgroup
+    uint32_t* bits;
+    TrajAccum* acc;
+};
+
 // ---- launchers (each defined next to its kernels) ----
 
 hipError_t launch_encode_map(const float* prob, uint32_t* enc, const DevMap& m, float occ_thr,
@@ -127,7 +151,7 @@ hipError_t launch_trace_paths(const DevMap& m, const CamParams& c, const float* 
                               int32_t* lin_out, uint32_t* len_out, hipStream_t s);
 
 hipError_t launch_traj_boxes(const DevMap& m, const CamParams& c, const float* poses, uint32_t T,
-                             uint32_t L, TrajBox* boxes, hipStream_t s);
+                             uint32_t L, TrajBox* boxes, const TrajSplit& split, hipStream_t s);
 
 // Static LDS of the union kernel (its reductions); the bitset gets the rest.
 size_t traj_static_lds_bytes();
@@ -140,7 +164,7 @@ const void* traj_union_kernel_ptr(int waves);
 hipError_t launch_traj_union(int waves, const DevMap& m, const CamParams& c, const float* poses, uint32_t L,
                              uint32_t T, uint32_t pass_words, const TrajBox* boxes, float* ig_union,
                              uint32_t* counts, unsigned long long* visits, nbt_ig_ray_digest* trace,
-                             hipStream_t s);
+                             const TrajSplit& split, hipStream_t s);
 
 // Kernel entry points of the persistent batched launch (for graph nodes).
 const void* batch_kernel_ptr(int waves, int depth, bool count);

@@ -114,6 +114,31 @@ static int ensure_traj_workspace(nbt_ig_ctx* ctx, size_t T, hipStream_t s) {
     return NBT_IG_OK;
 }
 
+// How a call of T trajectories of `tiles` ray tiles each is split: a wave
+// walks about two thirds of what one round of the chip (32 waves per CU)
+// would give it, so that a call has a round and a half or more of short
+// workgroups, between 2 tiles (below, clearing and merging a bitset per
+// workgroup costs more than it spreads: 16 trajectories of 12 poses of
+// 128x96 rays take 261 us at 1 tile, 193-210 at 2 to 6, 244 at 12) and 16 (200 of
+// 24 poses: 3.2 ms at 6, 2.85 at 16).  From kTrajSplitMost trajectories on
+// one workgroup each spreads as well (4096 x 24: 13.4 us a trajectory, split
+// 13.2).  Unsplit and split: 16 x 12 poses 3.5 ms and 0.20, 64 x 12 3.6 and
+// 0.57, 200 x 24 7.1 and 2.85, 1000 x 24 16.5 and 13.2.
+static TrajSplit plan_traj_split(const nbt_ig_ctx* ctx, uint32_t T, uint64_t tiles) {
+    TrajSplit sp{1, 1, 0, nullptr, nullptr};
+    const uint64_t waves = (uint64_t)ctx->traj_waves, cu = (uint64_t)ctx->cu_count;
+    if (T > kTrajSplitMost || !ctx->traj_bits) return sp;
+    const uint64_t per_wave = std::min<uint64_t>(std::max<uint64_t>(T * tiles / (48u * cu), 2u), 16u);
+    const uint32_t groups = (uint32_t)(tiles / (per_wave * waves));
+    if (groups < 2 || (uint64_t)T * groups * waves * 64u >= (1ull << 32)) return sp;
+    sp.groups = groups;
+    sp.parts = (uint32_t)std::min<uint64_t>((4u * cu + T - 1) / T, (uint64_t)kTrajParts);
+    sp.cap_words = std::min(kTrajSplitWords / T, kTrajSplitCap);
+    sp.bits = ctx->traj_bits;
+    sp.acc = ctx->traj_acc;
+    return sp;
+}
+
 size_t traj_lds_bytes(const nbt_ig_ctx* ctx) {
     const int k = ctx->traj_waves == 4 ? 0 : ctx->traj_waves == 8 ? 1 : 2;
     size_t b = ctx->lds_budget ? ctx->lds_budget : ctx->traj_lds_share[k];
@@ -258,9 +283,19 @@ int nbt_ig_ctx_create(int device, nbt_ig_ctx** out) {
             delete ctx;
             return hip_fail(e, "context workspace");
         }
+        // Scratch of split trajectory calls (without it they run unsplit).
+        if (hipMalloc(&ctx->traj_bits, (size_t)kTrajSplitWords * 4) != hipSuccess ||
+            hipMalloc(&ctx->traj_acc, kTrajSplitMost * sizeof(TrajAccum)) != hipSuccess) {
+            (void)hipGetLastError();
+            if (ctx->traj_bits) (void)hipFree(ctx->traj_bits);
+            ctx->traj_bits = nullptr;
+            ctx->traj_acc = nullptr;
+        }
         if (int rc = init_noalloc_scratch(device)) {
             (void)hipFree(ctx->ws);
             (void)hipFree(ctx->boxes);
+            if (ctx->traj_bits) (void)hipFree(ctx->traj_bits);
+            if (ctx->traj_acc) (void)hipFree(ctx->traj_acc);
             delete ctx;
             return rc;
         }
@@ -276,6 +311,8 @@ void nbt_ig_ctx_destroy(nbt_ig_ctx* ctx) {
     release_buffer(ctx->ws, ctx->ws_async, nullptr);
     release_buffer(ctx->boxes, ctx->boxes_async, nullptr);
     release_buffer(ctx->topk_keep, ctx->topk_async, nullptr);
+    if (ctx->traj_bits) (void)hipFree(ctx->traj_bits);
+    if (ctx->traj_acc) (void)hipFree(ctx->traj_acc);
     if (ctx->ws_async || ctx->boxes_async || ctx->topk_async) (void)hipStreamSynchronize(nullptr);
     delete ctx;
 }
@@ -495,12 +532,13 @@ static int eval_trajectories_impl(const nbt_ig_map* map, const nbt_ig_camera* ca
     if (!g.ok) return fail(NBT_IG_EDEVICE, "cannot select device %d", ctx->device);
     hipStream_t s = (hipStream_t)stream;
     if (int rc = ensure_traj_workspace(ctx, n_traj, s)) return rc;
-    hipError_t e = launch_traj_boxes(map->dm, c, poses, n_traj, poses_per_traj, ctx->boxes, s);
+    const TrajSplit split = plan_traj_split(ctx, n_traj, tiles);
+    hipError_t e = launch_traj_boxes(map->dm, c, poses, n_traj, poses_per_traj, ctx->boxes, split, s);
     if (e != hipSuccess) return hip_fail(e, "traj_box_kernel");
     const size_t lds = traj_lds_bytes(ctx);
     const uint32_t pass_words = (uint32_t)(lds / 4 - 2);
     e = launch_traj_union(waves, map->dm, c, poses, poses_per_traj, n_traj, pass_words, ctx->boxes, ig_union,
-                          counts, reinterpret_cast<unsigned long long*>(visits), trace, s);
+                          counts, reinterpret_cast<unsigned long long*>(visits), trace, split, s);
     if (e != hipSuccess)
         return fail(e == hipErrorOutOfMemory ? NBT_IG_ENOMEM : NBT_IG_EDEVICE,
                     "traj_union_kernel(%zu bytes of LDS of %zu): %s", lds, ctx->lds_max, hipGetErrorString(e));

@@ -174,11 +174,14 @@ __device__ __forceinline__ uint32_t walk_ray_mark(const DevMap& m, __amdgpu_buff
     return n;
 }
 
+// One workgroup per trajectory, its poses' apexes and corners dealt to the
+// threads (4096 x 24 poses: one thread per trajectory walked 120 points in a
+// row).  For a split call it also clears the trajectory's scratch.
 __global__ __launch_bounds__(256) void traj_box_kernel(DevMap m, CamParams c,
-                                                       const float* __restrict__ poses, uint32_t T,
-                                                       uint32_t L, TrajBox* __restrict__ boxes) {
-    const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= T) return;
+                                                       const float* __restrict__ poses,
+                                                       uint32_t L, TrajBox* __restrict__ boxes,
+                                                       TrajSplit split) {
+    const uint32_t t = blockIdx.x;
     const float org[3] = {m.ox, m.oy, m.oz};
     const int n[3] = {m.nx, m.ny, m.nz};
     const float u_lo = c.W > 1 ? -c.dh : 0.0f, u_hi = c.W > 1 ? c.dh : 0.0f;
@@ -186,23 +189,54 @@ __global__ __launch_bounds__(256) void traj_box_kernel(DevMap m, CamParams c,
     float lo[3] = {__builtin_inff(), __builtin_inff(), __builtin_inff()};
     float hi[3] = {-__builtin_inff(), -__builtin_inff(), -__builtin_inff()};
     bool unbounded = false;
-    for (uint32_t l = 0; l < L; ++l) {
+    for (uint64_t k = threadIdx.x; k < 5ull * L; k += blockDim.x) {
+        const uint32_t l = (uint32_t)(k / 5u);
+        const int q = (int)(k - 5ull * l);
         const float* p = poses + 12 * ((size_t)t * L + l);
-        for (int q = 0; q < 5; ++q) {
-            const float u = q == 0 ? 0.0f : ((q & 1) ? u_lo : u_hi);
-            const float v = q == 0 ? 0.0f : ((q & 2) ? v_lo : v_hi);
-            const float d = q == 0 ? 0.0f : c.range;
-            for (int a = 0; a < 3; ++a) {
-                float w = p[3 * a + 0] * u;
-                w = w + p[3 * a + 1] * v;
-                w = w + p[3 * a + 2] * d;
-                const float e = (q == 0) ? p[9 + a] : p[9 + a] + w;
-                const float vx = (e - org[a]) * m.inv_s;
-                if (!__builtin_isfinite(vx)) unbounded = true;
-                lo[a] = vx < lo[a] ? vx : lo[a];
-                hi[a] = vx > hi[a] ? vx : hi[a];
-            }
+        const float u = q == 0 ? 0.0f : ((q & 1) ? u_lo : u_hi);
+        const float v = q == 0 ? 0.0f : ((q & 2) ? v_lo : v_hi);
+        const float d = q == 0 ? 0.0f : c.range;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            float w = p[3 * a + 0] * u;
+            w = w + p[3 * a + 1] * v;
+            w = w + p[3 * a + 2] * d;
+            const float e = (q == 0) ? p[9 + a] : p[9 + a] + w;
+            const float vx = (e - org[a]) * m.inv_s;
+            if (!__builtin_isfinite(vx)) unbounded = true;
+            lo[a] = vx < lo[a] ? vx : lo[a];
+            hi[a] = vx > hi[a] ? vx : hi[a];
         }
+    }
+    __shared__ float s_lo[4][3], s_hi[4][3];
+    __shared__ int s_unbounded[4];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            lo[a] = fminf(lo[a], __shfl_xor(lo[a], o, 64));
+            hi[a] = fmaxf(hi[a], __shfl_xor(hi[a], o, 64));
+        }
+    }
+    const bool wave_unbounded = __ballot(unbounded) != 0ull;
+    const int wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            s_lo[wave][a] = lo[a];
+            s_hi[wave][a] = hi[a];
+        }
+        s_unbounded[wave] = wave_unbounded ? 1 : 0;
+    }
+    __syncthreads();
+    unbounded = false;
+    for (int w = 0; w < waves; ++w) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            lo[a] = fminf(lo[a], s_lo[w][a]);
+            hi[a] = fmaxf(hi[a], s_hi[w][a]);
+        }
+        unbounded = unbounded || s_unbounded[w] != 0;
     }
     int ilo[3], ihi[3];
     for (int a = 0; a < 3; ++a) {
@@ -221,7 +255,20 @@ __global__ __launch_bounds__(256) void traj_box_kernel(DevMap m, CamParams c,
     b.lx = ilo[0]; b.ly = ilo[1]; b.lz = ilo[2];
     b.ax = ihi[0] - ilo[0] + 1; b.ay = ihi[1] - ilo[1] + 1; b.az = ihi[2] - ilo[2] + 1;
     b.nbits = (L == 0) ? 0u : (uint32_t)b.ax * (uint32_t)b.ay * (uint32_t)b.az;
-    boxes[t] = b;
+    b.pad = 0u;
+    if (threadIdx.x == 0) boxes[t] = b;
+    if (split.groups > 1) {
+        const uint64_t words = ((uint64_t)b.nbits + 31u) / 32u;
+        if (words <= split.cap_words) {
+            uint32_t* bits = split.bits + (size_t)t * split.cap_words;
+            for (uint32_t w = threadIdx.x; w < (uint32_t)words; w += blockDim.x) bits[w] = 0u;
+        }
+        if (threadIdx.x == 0) {
+            split.acc[t].visits = 0ull;
+            split.acc[t].invalid = 0u;
+            split.acc[t].count = 0u;
+        }
+    }
 }
 
 // One workgroup per trajectory.  The bitset of its box is kept in LDS,
@@ -234,15 +281,25 @@ __global__ __launch_bounds__(256) void traj_box_kernel(DevMap m, CamParams c,
 // Eight waves per SIMD: the kernel fits 64 VGPRs, and left to itself the
 // compiler took 106 SGPRs, which allow only seven; with the hint it keeps 78
 // (the few spills are outside the walk) and four 8-wave workgroups fit a CU.
-template <int WAVES, bool COUNT, bool TRACE>
+//
+// SPLIT: few trajectories would leave most of the chip idle (16 of them used
+// 16 CUs), so split.groups workgroups share one trajectory.  Each walks a
+// contiguous run of the tile order (a few pixel tiles, all poses: the voxels
+// of different workgroups overlap little) into a bitset of its own and ORs
+// its nonzero words into the trajectory's bitset in memory; traj_sum_kernel
+// sums that up.  A box larger than the scratch is left to one workgroup.
+template <int WAVES, bool COUNT, bool TRACE, bool SPLIT>
 __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(8, 8))) void traj_union_kernel(
     DevMap m, CamParams c, const float* __restrict__ poses, uint32_t L,
     const TrajBox* __restrict__ boxes, uint32_t pass_words, float* __restrict__ ig_union,
     uint32_t* __restrict__ counts, unsigned long long* __restrict__ visits,
-    nbt_ig_ray_digest* __restrict__ trace) {
+    nbt_ig_ray_digest* __restrict__ trace, TrajSplit split) {
     extern __shared__ uint32_t lds_bits[];
-    const uint32_t t = blockIdx.x;
+    const uint32_t t = SPLIT ? blockIdx.x / split.groups : blockIdx.x;
     const TrajBox b = boxes[t];
+    const bool whole = !SPLIT || ((uint64_t)b.nbits + 31u) / 32u > split.cap_words;
+    const uint32_t part = SPLIT ? blockIdx.x - t * split.groups : 0u;
+    if (SPLIT && whole && part != 0u) return;
     // the bitset follows the walk's all-ones word and holds the clamp bit
     uint32_t* bits = lds_bits + 1;
     const uint32_t tid = threadIdx.x;
@@ -256,7 +313,11 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(8, 8
     tile_pixel(lane, 3, lx, ly);
     const uint32_t tiles_x = (uint32_t)(c.W + 7) / 8;
     const uint32_t tiles_pose = tiles_x * (uint32_t)((c.H + 7) / 8);
-    const uint32_t total = tiles_pose * L;
+    uint32_t tile0 = 0u, total = tiles_pose * L;
+    if (SPLIT && !whole) {
+        tile0 = (uint32_t)((uint64_t)total * part / split.groups);
+        total = (uint32_t)((uint64_t)total * (part + 1u) / split.groups);
+    }
     const uint64_t rays = (uint64_t)c.W * (uint64_t)c.H;
     const __amdgpu_buffer_rsrc_t rs = map_rsrc(m);
     uint32_t steps = 0;
@@ -271,7 +332,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(8, 8
         for (uint32_t w = tid; w <= nb / 32u; w += nthreads) bits[w] = 0u;
         __syncthreads();
 
-        for (uint32_t tile = (uint32_t)wave; tile < total; tile += WAVES) {
+        for (uint32_t tile = tile0 + (uint32_t)wave; tile < total; tile += WAVES) {
             // poses fastest: a workgroup's waves walk the same pixel tile of
             // consecutive poses together, whose rays meet mostly the same voxels
             const uint32_t tt = tile / L;
@@ -315,6 +376,17 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(8, 8
             }
         }
         __syncthreads();
+
+        if (SPLIT && !whole) {
+            uint32_t* all = split.bits + (size_t)t * split.cap_words + base / 32u;
+            for (uint32_t w = tid; w < (nb + 31u) / 32u; w += nthreads) {
+                uint32_t word = bits[w];
+                if (w == nb >> 5) word &= (1u << (nb & 31u)) - 1u;
+                if (word) atomicOr(all + w, word);
+            }
+            __syncthreads();   // the next pass clears the bitset
+            continue;
+        }
 
         // Epilogue of the slice: classify the voxels of U from their encoded words.
         const uint32_t base_w = base / 32u;                      // pass_bits is a multiple of 32
@@ -375,6 +447,11 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(8, 8
         cu += s_cnt[w][2];
         inv |= s_inv[w];
     }
+    if (SPLIT && !whole) {
+        if (COUNT && vs) atomicAdd(&split.acc[t].visits, vs);
+        if (inv) atomicOr(&split.acc[t].invalid, 1u);
+        return;
+    }
     ig_union[t] = inv ? __builtin_nanf("") : (float)g;
     counts[4 * (size_t)t + 0] = co + cf + cu;
     counts[4 * (size_t)t + 1] = co;
@@ -383,54 +460,150 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(8, 8
     if (visits) visits[t] = vs;
 }
 
+// Sums up the bitset that the workgroups of a split trajectory marked: the
+// rows of its box dealt to the waves of split.parts workgroups, one lane per
+// voxel of a row.  Each part leaves its sums in the trajectory's slot and the
+// last one adds them in a fixed order, so the result does not depend on which
+// that is; slot and count are only touched by atomic read-modify-writes, the
+// count's held until the sums' have returned (as in the perspectives' combine).
+constexpr int kTrajSumWaves = 4;
+__global__ __launch_bounds__(kTrajSumWaves * 64) void traj_sum_kernel(
+    DevMap m, const TrajBox* __restrict__ boxes, float* __restrict__ ig_union, uint32_t* __restrict__ counts,
+    unsigned long long* __restrict__ visits, TrajSplit split) {
+    const uint32_t t = blockIdx.x / split.parts, part = blockIdx.x - t * split.parts;
+    const TrajBox b = boxes[t];
+    if (((uint64_t)b.nbits + 31u) / 32u > split.cap_words) return;      // one workgroup did it all
+    const uint32_t* bits = split.bits + (size_t)t * split.cap_words;
+    const int lane = threadIdx.x & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const __amdgpu_buffer_rsrc_t rs = map_rsrc(m);
+    uint32_t c_occ = 0, c_free = 0, c_unk = 0;
+    double gain = 0.0;
+    const uint32_t rows = b.nbits == 0u ? 0u : (uint32_t)b.ay * (uint32_t)b.az;
+    for (uint32_t r = part * kTrajSumWaves + wave; r < rows; r += split.parts * kTrajSumWaves) {
+        const int z = (int)(r / (uint32_t)b.ay), y = (int)(r - (uint32_t)z * (uint32_t)b.ay);
+        for (int x = lane; x < b.ax; x += 64) {
+            const uint32_t p = r * (uint32_t)b.ax + (uint32_t)x;
+            if (!((bits[p >> 5] >> (p & 31u)) & 1u)) continue;
+            const uint32_t e = load_word(rs, voxel_offset(m, b.lx + x, b.ly + y, b.lz + z));
+            gain += (double)__uint_as_float(e & ~kOccBit);
+            if (e & kOccBit) ++c_occ;
+            else if (e == kGainOne) ++c_unk;
+            else ++c_free;
+        }
+    }
+    gain = wave_sum(gain);
+    c_occ = wave_sum_u32(c_occ);
+    c_free = wave_sum_u32(c_free);
+    c_unk = wave_sum_u32(c_unk);
+    __shared__ double s_gain[kTrajSumWaves];
+    __shared__ uint32_t s_cnt[kTrajSumWaves][3];
+    if (lane == 0) {
+        s_gain[wave] = gain;
+        s_cnt[wave][0] = c_occ;
+        s_cnt[wave][1] = c_free;
+        s_cnt[wave][2] = c_unk;
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    TrajAccum* a = split.acc + t;
+    unsigned int done = 0u;
+    if (lane == 0) {
+        double g = 0.0;
+        unsigned long long co = 0, cf = 0, cu = 0;
+#pragma unroll
+        for (int w = 0; w < kTrajSumWaves; ++w) {
+            g += s_gain[w];
+            co += s_cnt[w][0];
+            cf += s_cnt[w][1];
+            cu += s_cnt[w][2];
+        }
+        const unsigned long long o_g = atomicExch(&a->gain[part], (unsigned long long)__double_as_longlong(g));
+        const unsigned long long o_c = atomicExch(&a->occ_free[part], co | cf << 32);
+        const unsigned long long o_u = atomicExch(&a->unknown[part], cu);
+        unsigned int one = 1u;
+        asm volatile("" : "+v"(one) : "v"(o_g), "v"(o_c), "v"(o_u));
+        done = atomicAdd(&a->count, one);
+    }
+    done = (unsigned int)__shfl((int)done, 0, 64);
+    if (done != split.parts - 1u) return;
+    double g = 0.0;
+    unsigned long long of = 0ull, un = 0ull;
+    if ((uint32_t)lane < split.parts) {
+        g = __longlong_as_double((long long)atomicAdd(&a->gain[lane], 0ull));
+        of = atomicAdd(&a->occ_free[lane], 0ull);
+        un = atomicAdd(&a->unknown[lane], 0ull);
+    }
+    g = wave_sum(g);
+    const uint32_t co = wave_sum_u32((uint32_t)of), cf = wave_sum_u32((uint32_t)(of >> 32));
+    const uint32_t cu = wave_sum_u32((uint32_t)un);
+    if (lane != 0) return;
+    ig_union[t] = a->invalid ? __builtin_nanf("") : (float)g;
+    counts[4 * (size_t)t + 0] = co + cf + cu;
+    counts[4 * (size_t)t + 1] = co;
+    counts[4 * (size_t)t + 2] = cf;
+    counts[4 * (size_t)t + 3] = cu;
+    if (visits) visits[t] = a->visits;
+}
+
 size_t traj_static_lds_bytes() {
     // the largest static LDS among the workgroup sizes (the 16-wave kernel)
     hipFuncAttributes a;
-    if (hipFuncGetAttributes(&a, (const void*)traj_union_kernel<16, true, true>) != hipSuccess) return 4096;
+    if (hipFuncGetAttributes(&a, (const void*)traj_union_kernel<16, true, true, false>) != hipSuccess) return 4096;
     return a.sharedSizeBytes;
 }
 
 const void* traj_union_kernel_ptr(int waves) {
     switch (waves) {
-    case 4: return (const void*)traj_union_kernel<4, false, false>;
-    case 8: return (const void*)traj_union_kernel<8, false, false>;
-    case 16: return (const void*)traj_union_kernel<16, false, false>;
+    case 4: return (const void*)traj_union_kernel<4, false, false, false>;
+    case 8: return (const void*)traj_union_kernel<8, false, false, false>;
+    case 16: return (const void*)traj_union_kernel<16, false, false, false>;
     default: return nullptr;
     }
 }
 
 hipError_t launch_traj_boxes(const DevMap& m, const CamParams& c, const float* poses, uint32_t T,
-                             uint32_t L, TrajBox* boxes, hipStream_t s) {
-    hipLaunchKernelGGL(traj_box_kernel, dim3((T + 255) / 256), dim3(256), 0, s, m, c, poses, T, L, boxes);
+                             uint32_t L, TrajBox* boxes, const TrajSplit& split, hipStream_t s) {
+    // a split call's scratch is cleared here too: more threads
+    hipLaunchKernelGGL(traj_box_kernel, dim3(T), dim3(split.groups > 1 ? 256 : 64), 0, s, m, c, poses, L, boxes,
+                       split);
     return hipGetLastError();
 }
 
-template <int WAVES, bool COUNT, bool TRACE>
+template <int WAVES, bool COUNT, bool TRACE, bool SPLIT>
 static hipError_t launch_union(const DevMap& m, const CamParams& c, const float* poses, uint32_t L,
                                uint32_t T, uint32_t pass_words, const TrajBox* boxes, float* ig_union,
                                uint32_t* counts, unsigned long long* visits, nbt_ig_ray_digest* trace,
-                               hipStream_t s) {
-    const void* k = (const void*)traj_union_kernel<WAVES, COUNT, TRACE>;
+                               const TrajSplit& split, hipStream_t s) {
+    const void* k = (const void*)traj_union_kernel<WAVES, COUNT, TRACE, SPLIT>;
     // the all-ones word, pass_words words of the slice and the word of its clamp bit
     const size_t lds = ((size_t)pass_words + 2) * 4;
     static std::atomic<size_t> lds_set[64];
-    const hipError_t e = allow_dynamic_lds(k, lds, lds_set, 64);
+    hipError_t e = allow_dynamic_lds(k, lds, lds_set, 64);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((traj_union_kernel<WAVES, COUNT, TRACE>), dim3(T), dim3(WAVES * 64), lds, s, m, c,
-                       poses, L, boxes, pass_words, ig_union, counts, visits, trace);
+    hipLaunchKernelGGL((traj_union_kernel<WAVES, COUNT, TRACE, SPLIT>), dim3(SPLIT ? T * split.groups : T),
+                       dim3(WAVES * 64), lds, s, m, c, poses, L, boxes, pass_words, ig_union, counts, visits, trace,
+                       split);
+    e = hipGetLastError();
+    if (!SPLIT || e != hipSuccess) return e;
+    hipLaunchKernelGGL(traj_sum_kernel, dim3(T * split.parts), dim3(kTrajSumWaves * 64), 0, s, m, boxes, ig_union,
+                       counts, visits, split);
     return hipGetLastError();
 }
 
 hipError_t launch_traj_union(int waves, const DevMap& m, const CamParams& c, const float* poses, uint32_t L,
                              uint32_t T, uint32_t pass_words, const TrajBox* boxes, float* ig_union,
                              uint32_t* counts, unsigned long long* visits, nbt_ig_ray_digest* trace,
-                             hipStream_t s) {
+                             const TrajSplit& split, hipStream_t s) {
     const bool count = visits != nullptr;    // no visit count when the caller does not ask for it
     const bool tr = trace != nullptr;
-#define NBT_TU(W, C, R)                                                                              \
-    if (waves == W && count == C && tr == R)                                                         \
-        return launch_union<W, C, R>(m, c, poses, L, T, pass_words, boxes, ig_union, counts, visits, \
-                                     trace, s);
+    const bool sp = split.groups > 1;
+#define NBT_TU(W, C, R)                                                                                     \
+    if (waves == W && count == C && tr == R)                                                                \
+        return sp ? launch_union<W, C, R, true>(m, c, poses, L, T, pass_words, boxes, ig_union, counts,     \
+                                                visits, trace, split, s)                                    \
+                  : launch_union<W, C, R, false>(m, c, poses, L, T, pass_words, boxes, ig_union, counts,    \
+                                                 visits, trace, split, s);
     NBT_TU(4, true, false) NBT_TU(8, true, false) NBT_TU(16, true, false)
     NBT_TU(4, false, false) NBT_TU(8, false, false) NBT_TU(16, false, false)
     NBT_TU(4, true, true) NBT_TU(8, true, true) NBT_TU(16, true, true)
