@@ -70,7 +70,8 @@ struct nbt_ig_ctx {
     nbt::TrajBox* boxes = nullptr;
     size_t boxes_bytes = 0;
     bool boxes_async = false;
-    // scratch of split trajectory calls: bitsets and per-trajectory slots, of one fixed size
+    // scratch of split trajectory calls: bitsets and per-trajectory slots, of one
+    // fixed size, allocated by the first such call
     uint32_t* traj_bits = nullptr;
     nbt::TrajAccum* traj_acc = nullptr;
     unsigned long long* topk_keep = nullptr;   // top-k selection scratch

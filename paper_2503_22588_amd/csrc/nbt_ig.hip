@@ -114,6 +114,33 @@ static int ensure_traj_workspace(nbt_ig_ctx* ctx, size_t T, hipStream_t s) {
     return NBT_IG_OK;
 }
 
+// Scratch of split trajectory calls: one fixed size, allocated by the first
+// such call (80 us; context creation stays as it was).  False without it: no memory, or the
+// stream is being captured and must not meet an allocation; the call then
+// runs unsplit.
+static bool ensure_traj_scratch(nbt_ig_ctx* ctx, hipStream_t s) {
+    std::lock_guard<std::mutex> lk(ctx->mu);
+    if (ctx->traj_acc) return true;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return false;
+    }
+    // another thread may be capturing a stream of its own meanwhile
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    hipError_t e = hipMalloc(&ctx->traj_bits, (size_t)kTrajSplitWords * 4);
+    if (e == hipSuccess) e = hipMalloc(&ctx->traj_acc, kTrajSplitMost * sizeof(TrajAccum));
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        if (ctx->traj_bits) (void)hipFree(ctx->traj_bits);
+        ctx->traj_bits = nullptr;
+        ctx->traj_acc = nullptr;
+    }
+    if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return e == hipSuccess;
+}
+
 // How a call of T trajectories of `tiles` ray tiles each is split: a wave
 // walks about two thirds of what one round of the chip (32 waves per CU)
 // would give it, so that a call has a round and a half or more of short
@@ -124,13 +151,14 @@ static int ensure_traj_workspace(nbt_ig_ctx* ctx, size_t T, hipStream_t s) {
 // one workgroup each spreads as well (4096 x 24: 13.4 us a trajectory, split
 // 13.2).  Unsplit and split: 16 x 12 poses 3.5 ms and 0.20, 64 x 12 3.6 and
 // 0.57, 200 x 24 7.1 and 2.85, 1000 x 24 16.5 and 13.2.
-static TrajSplit plan_traj_split(const nbt_ig_ctx* ctx, uint32_t T, uint64_t tiles) {
+static TrajSplit plan_traj_split(nbt_ig_ctx* ctx, uint32_t T, uint64_t tiles, hipStream_t s) {
     TrajSplit sp{1, 1, 0, nullptr, nullptr};
     const uint64_t waves = (uint64_t)ctx->traj_waves, cu = (uint64_t)ctx->cu_count;
-    if (T > kTrajSplitMost || !ctx->traj_bits) return sp;
+    if (T > kTrajSplitMost) return sp;
     const uint64_t per_wave = std::min<uint64_t>(std::max<uint64_t>(T * tiles / (48u * cu), 2u), 16u);
     const uint32_t groups = (uint32_t)(tiles / (per_wave * waves));
     if (groups < 2 || (uint64_t)T * groups * waves * 64u >= (1ull << 32)) return sp;
+    if (!ensure_traj_scratch(ctx, s)) return sp;
     sp.groups = groups;
     sp.parts = (uint32_t)std::min<uint64_t>((4u * cu + T - 1) / T, (uint64_t)kTrajParts);
     sp.cap_words = std::min(kTrajSplitWords / T, kTrajSplitCap);
@@ -283,19 +311,9 @@ int nbt_ig_ctx_create(int device, nbt_ig_ctx** out) {
             delete ctx;
             return hip_fail(e, "context workspace");
         }
-        // Scratch of split trajectory calls (without it they run unsplit).
-        if (hipMalloc(&ctx->traj_bits, (size_t)kTrajSplitWords * 4) != hipSuccess ||
-            hipMalloc(&ctx->traj_acc, kTrajSplitMost * sizeof(TrajAccum)) != hipSuccess) {
-            (void)hipGetLastError();
-            if (ctx->traj_bits) (void)hipFree(ctx->traj_bits);
-            ctx->traj_bits = nullptr;
-            ctx->traj_acc = nullptr;
-        }
         if (int rc = init_noalloc_scratch(device)) {
             (void)hipFree(ctx->ws);
             (void)hipFree(ctx->boxes);
-            if (ctx->traj_bits) (void)hipFree(ctx->traj_bits);
-            if (ctx->traj_acc) (void)hipFree(ctx->traj_acc);
             delete ctx;
             return rc;
         }
@@ -532,7 +550,7 @@ static int eval_trajectories_impl(const nbt_ig_map* map, const nbt_ig_camera* ca
     if (!g.ok) return fail(NBT_IG_EDEVICE, "cannot select device %d", ctx->device);
     hipStream_t s = (hipStream_t)stream;
     if (int rc = ensure_traj_workspace(ctx, n_traj, s)) return rc;
-    const TrajSplit split = plan_traj_split(ctx, n_traj, tiles);
+    const TrajSplit split = plan_traj_split(ctx, n_traj, tiles, s);
     hipError_t e = launch_traj_boxes(map->dm, c, poses, n_traj, poses_per_traj, ctx->boxes, split, s);
     if (e != hipSuccess) return hip_fail(e, "traj_box_kernel");
     const size_t lds = traj_lds_bytes(ctx);
