@@ -60,7 +60,7 @@ struct nbt_ig_ctx {
     nbt::VpAccum* ws = nullptr;          // per-perspective reduction slots, kept zeroed
     size_t ws_bytes = 0;
     bool ws_async = false;
-    nbt::VpLaunch vp_launch{4, 3, 0, 0, 8};  // 4 waves, 8x8 tiles, tiles/wave balanced per camera, no remap, 8 gathers in flight
+    nbt::VpLaunch vp_launch;         // 4 waves, 8x8 tiles, tiles/wave balanced per camera, no remap, 8 gathers in flight
     size_t lds_max = 0;             // device limit of LDS per workgroup (bytes)
     size_t lds_budget = 0;          // LDS a trajectory bitset may use (bytes); 0 = traj_lds_share
     size_t traj_lds_share[3] = {0, 0, 0};  // LDS per workgroup that keeps the union kernel's occupancy (4/8/16 waves)

@@ -86,11 +86,24 @@ constexpr double kFixScale = 16777216.0;     // 2^24
 
 // Launch shape of the viewpoint kernel.
 struct VpLaunch {
-    int waves;              // waves per workgroup (1, 2, 4, 8)
-    int tile_w_log2;        // pixel tile of one wave: (1<<tile_w_log2) x (64>>tile_w_log2)
-    int tiles_per_wave;     // tiles one wave walks per workgroup; 0 = balanced for the camera
-    int xcd_remap;          // 0, or runs of this many consecutive workgroups per XCD
-    int depth;              // gathers in flight per lane (1, 2, 4, 8)
+    int waves = 4;          // waves per workgroup (1, 2, 4, 8)
+    int tile_w_log2 = 3;    // pixel tile of one wave: (1<<tile_w_log2) x (64>>tile_w_log2)
+    int tiles_per_wave = 0; // tiles one wave walks per workgroup; 0 = balanced for the camera
+    int xcd_remap = 0;      // 0, or runs of this many consecutive workgroups per XCD
+    int depth = 8;          // gathers in flight per lane (1, 2, 4, 8)
+    bool operator==(const VpLaunch& o) const {
+        return waves == o.waves && tile_w_log2 == o.tile_w_log2 && tiles_per_wave == o.tiles_per_wave &&
+               xcd_remap == o.xcd_remap && depth == o.depth;
+    }
+};
+
+// Shape of a call whose rays are walked in segments (ig_segments_kernel).
+struct SegLaunch {
+    int segs_log2;          // segments per ray; -1: the rays are not split
+    int rays_log2;          // rays of a workgroup; its threads are rays * segments
+    int flat;               // rays dealt in row-major order, else in square-ish pixel tiles
+    uint32_t blocks;        // blocks of 8 crossings per axis and ray that the LDS table holds
+    uint32_t groups;        // workgroups per perspective
 };
 
 // Voxel box of one trajectory's frusta (its bitset positions: x fastest).
@@ -138,6 +151,11 @@ hipError_t launch_eval_viewpoints(const DevMap& m, const CamParams& c, const flo
                                   uint32_t n, float* ig_out, unsigned long long* steps_out,
                                   VpAccum* ws, const VpLaunch& L, hipStream_t s,
                                   nbt_ig_ray_digest* trace = nullptr);
+
+SegLaunch plan_segments(const DevMap& m, const CamParams& c, uint32_t n, int cu_count);
+hipError_t launch_eval_segments(const DevMap& m, const CamParams& c, const float* poses, uint32_t n,
+                                float* ig_out, unsigned long long* steps_out, VpAccum* ws, const SegLaunch& L,
+                                hipStream_t s, nbt_ig_ray_digest* trace);
 
 // Zeroes n per-perspective reduction slots (a fill kernel: no memset node
 // when the caller captures the stream).

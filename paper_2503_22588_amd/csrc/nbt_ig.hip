@@ -483,7 +483,10 @@ static int eval_viewpoints_impl(const nbt_ig_map* map, const nbt_ig_camera* cam,
     if (!poses || !ig_out) return fail(NBT_IG_EINVAL, "poses or ig_out is NULL");
     nbt_ig_ctx* ctx = map->ctx;
     const VpLaunch L = resolve_launch(c, ctx->vp_launch, n, ctx->cu_count);
-    const uint64_t groups = vp_groups(c, L);
+    // A launch shape that was set or tuned is kept; the default one walks the rays of a small call in segments.
+    SegLaunch seg{-1, 0, 0, 0, 0};
+    if (ctx->vp_launch == VpLaunch{}) seg = plan_segments(map->dm, c, n, ctx->cu_count);
+    const uint64_t groups = seg.segs_log2 > 0 ? seg.groups : vp_groups(c, L);
     if ((uint64_t)n * groups * (uint64_t)(L.waves * 64) >= (1ull << 32))
         return fail(NBT_IG_EUNSUPPORTED, "%u perspectives x %llu workgroups exceed the grid limit", n,
                     (unsigned long long)groups);
@@ -507,8 +510,10 @@ static int eval_viewpoints_impl(const nbt_ig_map* map, const nbt_ig_camera* cam,
         if (int rc = ensure_workspace(ctx, n, s)) return rc;
         ws = ctx->ws;
     }
-    hipError_t e = launch_eval_viewpoints(map->dm, c, poses, n, ig_out,
-                                          reinterpret_cast<unsigned long long*>(steps_out), ws, L, s, trace);
+    unsigned long long* steps = reinterpret_cast<unsigned long long*>(steps_out);
+    const hipError_t e = seg.segs_log2 > 0
+                             ? launch_eval_segments(map->dm, c, poses, n, ig_out, steps, ws, seg, s, trace)
+                             : launch_eval_viewpoints(map->dm, c, poses, n, ig_out, steps, ws, L, s, trace);
     if (e != hipSuccess) return hip_fail(e, "ig_viewpoints_kernel");
     return NBT_IG_OK;
 }

@@ -455,4 +455,70 @@ __device__ __forceinline__ void walk_ray_pipelined(const DevMap& m, __amdgpu_buf
     if constexpr (traced<TR>()) tr->finish();
 }
 
+// walk_ray_pipelined over one stretch of a ray: starting at the state in `r`,
+// which is that of slot index K of the ray, it passes `skip` slots without
+// visiting them and then visits `groups` groups of kRunSlots slots (fewer
+// when the ray ends).  K + skip is a multiple of kRunSlots, so the runs that
+// are summed in binary32 are those of the whole walk.  Returns whether the
+// ray ended here: an Occupied voxel, the border or the segment's end.
+template <bool COUNT, int TL, class TR = NoTrace>
+__device__ __forceinline__ bool walk_ray_stretch(const DevMap& m, __amdgpu_buffer_rsrc_t rs, const RayState& r,
+                                                 uint32_t skip, uint32_t groups, double& acc, uint32_t& steps,
+                                                 TR* tr = nullptr) {
+    constexpr int P = kRunSlots;
+    const OffsetSteps o = offset_steps<TL>(m, r);
+    const float dtx = r.dtx, dty = r.dty, dtz = r.dtz;
+    const float t1 = r.t1;
+    uint32_t off = voxel_offset(m, r.ix, r.iy, r.iz);
+    float tx = r.tx, ty = r.ty, tz = r.tz;
+    bool alive = true;
+    auto advance = [&] {
+        dda_advance<TL>(tx, ty, tz, off, alive, t1, o.dx, o.dy, o.dz, o.bigx, o.bigy, o.flip, dtx, dty, dtz);
+    };
+    for (; skip > 0; --skip) advance();
+
+    uint32_t w[P];
+    [[maybe_unused]] uint32_t wo[P];
+    [[maybe_unused]] bool wl[P];
+#pragma unroll
+    for (int u = 0; u < P; ++u) {
+        if (u > 0) advance();
+        w[u] = load_word(rs, off);
+        if constexpr (traced<TR>()) {
+            wo[u] = off;
+            wl[u] = alive;
+        }
+    }
+    uint32_t n = 0;
+    bool run = groups != 0u;
+    bool over = false;
+    while (run) {
+        float part = 0.0f;
+#pragma unroll
+        for (int u = 0; u < P; ++u) {
+            const uint32_t x = w[u];
+            const bool take = run && x != kSentinel;
+            uint32_t xs = take ? x : 0u;
+            asm volatile("" : "+v"(xs));          // as in walk_ray_pipelined
+            part += fabsf(__uint_as_float(xs));
+            if constexpr (COUNT) n += take ? 1u : 0u;
+            if constexpr (traced<TR>()) {
+                if (run) tr->consume(m, x, wo[u], wl[u], t1);
+            }
+            run = run && (int)x >= 0;
+            advance();
+            w[u] = load_word(rs, off);
+            if constexpr (traced<TR>()) {
+                wo[u] = off;
+                wl[u] = alive;
+            }
+        }
+        acc += (double)part;
+        over = !run;
+        run = run && --groups != 0u;
+    }
+    if constexpr (COUNT) steps += n;
+    return over;
+}
+
 }  // namespace nbt
