@@ -1,6 +1,8 @@
 """GPU checks of the map update at the edges of its kernels: encoding of maps around the tile and
 layer steps in every order (against the plain encoding of the linear order, rewritten by the
-separate re-layout kernel)."""
+separate re-layout kernel), and depth insertion at image sizes beside the 16x16-pixel groups, voxel
+counts that are no multiple of 8, arrays that are not 16-byte aligned, a map of more than 512
+voxels on an axis, and rays along the axes and beside the map's faces (against the oracle)."""
 
 import numpy as np
 import pytest
@@ -66,3 +68,40 @@ def test_encoding(nbt, shape):
             m.check()
     ctx.close()
 
+
+@pytest.mark.parametrize("shape,w,h", [((17, 19, 13), 1, 1), ((17, 19, 13), 16, 16), ((33, 20, 9), 17, 31),
+                                       ((600, 21, 15), 33, 15), ((40, 41, 43), 50, 2)],
+                         ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+@pytest.mark.parametrize("shift", [0, 1])
+def test_insertion(nbt, shape, w, h, shift):
+    import torch
+    print(f"[gpu] insertion {shape} {w}x{h} shift {shift}", flush=True)
+    sc = _scene(shape, seed=shape[1])
+    rng = np.random.default_rng(w + h)
+    cam = Camera(w, h, 80.0, 70.0, 6.0)
+    poses = poses_ball(sc.poi, 0.045 * min(shape), 6, seed=5)
+    poses[0, :9] = np.eye(3, dtype=np.float32).ravel()        # along an axis
+    poses[1] = look_at(sc.poi[None], sc.poi + np.array([1.0, 0, 0]))[0]
+    poses[2] = look_at(np.array([[-1.0, 0.7, 0.5]]), sc.poi)[0]      # from outside the map
+    depth = rng.uniform(0.05, 7.0, size=(6, h, w)).astype(np.float32)
+    depth[rng.random(depth.shape) < 0.2] = np.inf
+    depth[rng.random(depth.shape) < 0.05] = np.nan
+    L0 = rng.uniform(-2.5, 4.0, size=sc.P.shape).astype(np.float32)
+    ctx = nbt.Context(0)
+    m = nbt.Map(ctx, sc.P, sc.voxel, sc.origin)
+    n = L0.size
+
+    def placed(a):                                            # `shift` floats off a 16-byte boundary
+        t = torch.zeros(n + shift, dtype=torch.float32, device="cuda")[shift:].view(sc.P.shape)
+        t.copy_(torch.from_numpy(a))
+        return t
+
+    L, prob = placed(L0), placed(L0)
+    nbt.insert_scans(m, cam, torch.from_numpy(poses).cuda(), torch.from_numpy(depth).cuda(), L, prob_out=prob)
+    torch.cuda.synchronize()
+    ref = oracle.insert_scans(sc, cam, poses, depth, L0)
+    assert np.array_equal(L.cpu().numpy().view(np.uint32), ref.view(np.uint32))
+    p = 1.0 / (1.0 + np.exp(-ref.astype(np.float64)))
+    assert np.all(np.abs(prob.cpu().numpy() - p) <= 4 * np.spacing(p.astype(np.float32)))
+    assert int(m._insert_ws.abs().sum()) == 0
+    ctx.close()
