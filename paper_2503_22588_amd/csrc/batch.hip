@@ -16,6 +16,7 @@ struct nbt_ig_batch {
     unsigned int* queue = nullptr;      // work-queue head (device)
     VpAccum* ws = nullptr;              // per-perspective reduction slots, kept zeroed
     uint32_t grid = 0;                  // persistent workgroups
+    bool coded = false;                 // some of the maps have codes
     // the captured launch and the arguments it was built for
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -33,7 +34,7 @@ void drop_graph(nbt_ig_batch* b) {
 }
 
 int set_batch_launch(nbt_ig_batch* b, const VpLaunch& L) {
-    const void* k = batch_kernel_ptr(L.waves, L.depth, true);
+    const void* k = batch_kernel_ptr(L.waves, L.depth, true, b->coded);
     if (!k) return fail(NBT_IG_EINVAL, "unsupported batch launch shape");
     int per_cu = 0;
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, L.waves * 64, 0);
@@ -78,7 +79,7 @@ int build_graph(nbt_ig_batch* b, const uint32_t* offsets, const float* poses, fl
     void* args[] = {&maps, &n_maps, &offsets, &cap, &cam, &poses, &groups, &tiles_x, &tiles,
                     &tw_log2, &tpw, &queue, &ig_out, &steps_out, &ws};
     hipKernelNodeParams run{};
-    run.func = const_cast<void*>(batch_kernel_ptr(L.waves, L.depth, steps_out != nullptr));
+    run.func = const_cast<void*>(batch_kernel_ptr(L.waves, L.depth, steps_out != nullptr, b->coded));
     run.gridDim = dim3(b->grid);
     run.blockDim = dim3(L.waves * 64);
     run.sharedMemBytes = 0;
@@ -193,10 +194,12 @@ int nbt_ig_batch_create(nbt_ig_ctx* ctx, const nbt_ig_map* const* maps, uint32_t
     CamParams c;
     if (int rc = check_camera(cam, &c)) return rc;
     std::vector<DevMap> table(n_maps);
+    bool coded = false;
     for (uint32_t k = 0; k < n_maps; ++k) {
         if (int rc = check_map(maps[k])) return rc;
         if (maps[k]->ctx != ctx) return fail(NBT_IG_EINVAL, "map %u belongs to another context", k);
         table[k] = maps[k]->dm;
+        coded = coded || maps[k]->dm.codes != nullptr;
     }
     const uint64_t groups = vp_groups(c, ctx->vp_launch);
     if ((uint64_t)max_total_viewpoints * groups >= (1ull << 32))
@@ -209,6 +212,7 @@ int nbt_ig_batch_create(nbt_ig_ctx* ctx, const nbt_ig_map* const* maps, uint32_t
     b->n_maps = n_maps;
     b->cam = c;
     b->capacity = max_total_viewpoints;
+    b->coded = coded;
     hipError_t e = hipMalloc(&b->d_maps, n_maps * sizeof(DevMap));
     if (e == hipSuccess) e = hipMemcpy(b->d_maps, table.data(), n_maps * sizeof(DevMap), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMalloc(&b->queue, 256);

@@ -85,6 +85,7 @@ struct nbt_ig_map {
     nbt::DevMap dm{};
     uint32_t* enc = nullptr;
     size_t enc_bytes = 0;
+    void* codes = nullptr;          // the codes, then the palette and its flag; may be absent
     float voxel = 0.0f;
     float origin[3] = {0, 0, 0};
     nbt_ig_classify cls{0.5f, 0.5f};

@@ -42,6 +42,30 @@ __host__ __device__ inline int layout_tile_log2(int layout) {
 }
 inline bool valid_layout(int layout) { return layout >= NBT_IG_LAYOUT_LINEAR && layout <= NBT_IG_LAYOUT_COLUMN8; }
 
+// A map also holds one byte per voxel, its code: the index of its word in a
+// palette of the map's distinct words (kCodes entries; 0 is the sentinel, 1
+// Unknown, the others filled by the encoding, free ones hold kCodeFree).  The
+// perspective walk gathers codes and looks the words up in LDS, so a cache
+// line holds four times the voxels.  Words and codes say the same; a map with more
+// distinct words than the palette takes has its overflow flag set (the word
+// after the palette) and is walked by its words.
+//
+// The byte offset of a voxel is made of bit fields of X, Y and Z: x0 x1 y0 z0
+// y1 z1 x2 y2 z2 from bit 0, then the rest of X, of Y and of Z (16 bytes hold
+// a block of 4x2x2 voxels, a 128-byte line 8x4x4).  With the fields of the
+// axes that a ray follows backwards complemented, every step of the ray adds
+// one to its axis' field: ((g | ~mask) + 1) & mask within mask, the same four
+// operations for each axis, where strides would need a test for the tile's
+// face.
+constexpr uint32_t kCodes = 256;
+constexpr uint32_t kCodeFree = 0xFFFFFFFFu;
+
+__host__ __device__ inline uint32_t code_offset(int sy, int sz, uint32_t X, uint32_t Y, uint32_t Z) {
+    const uint32_t lo = (X & 3u) | (Y & 1u) << 2 | (Z & 1u) << 3 | (Y & 2u) << 3 | (Z & 2u) << 4 | (X & 4u) << 4 |
+                        (Y & 4u) << 5 | (Z & 4u) << 6;
+    return lo | (X >> 3) << 9 | (Y >> 3) << sy | (Z >> 3) << sz;
+}
+
 // Device view of an encoded map (passed to kernels by value).
 struct DevMap {
     const uint32_t* enc;    // encoded words in `layout` order
@@ -53,6 +77,11 @@ struct DevMap {
     int nbx, nby;           // tiles per axis over the padded x-y plane (column orders)
     float inv_s;            // 1/voxel_size (binary32)
     float ox, oy, oz;       // origin
+    const uint8_t* codes;   // nullptr: the map has none
+    const uint32_t* palette;    // kCodes words, then the overflow flag
+    uint32_t code_bytes;    // size of codes in bytes
+    uint32_t mx, my, mz;    // offset bits of each axis
+    int csy, csz;           // lowest offset bit of Y >> 3 and of Z >> 3
 };
 
 // Byte offset of voxel (x, y, z), real coordinates in [-1, n] (the border
@@ -140,6 +169,7 @@ struct TrajSplit {
 
 // ---- launchers (each defined next to its kernels) ----
 
+// Writes m's words (enc) and, when it has them, its codes and palette.
 hipError_t launch_encode_map(const float* prob, uint32_t* enc, const DevMap& m, float occ_thr,
                              float free_thr, unsigned int* bad_flag, hipStream_t s);
 // Copies an encoded map into another storage order (dst laid out as dstm).
@@ -185,7 +215,8 @@ hipError_t launch_traj_union(int waves, const DevMap& m, const CamParams& c, con
                              const TrajSplit& split, hipStream_t s);
 
 // Kernel entry points of the persistent batched launch (for graph nodes).
-const void* batch_kernel_ptr(int waves, int depth, bool count);
+// coded: some of the maps have codes.
+const void* batch_kernel_ptr(int waves, int depth, bool count, bool coded);
 const void* batch_reset_ptr();
 
 hipError_t launch_eval_cost(const float* id_pos, const float* id_ig, uint32_t nb, uint32_t np, float p,

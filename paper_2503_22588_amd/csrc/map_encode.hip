@@ -22,6 +22,98 @@ __device__ __forceinline__ uint32_t encode_prob(float p, float occ_thr, float fr
     return kGainOne;
 }
 
+// The palette of the map being encoded, copied to LDS: a word's code is the
+// slot it is found in, from a hash of the word on.  The sampling pass has
+// entered the words of kSampleCount voxels; a word it missed takes the first free slot by
+// compare-and-swap on the palette in memory, so all workgroups agree (the
+// copy only ever lags behind), one lane of a wave at a time: the others
+// usually wait for the same word.  A search of kCodeProbes slots without
+// success sets the overflow flag, and from then on no code matters.
+constexpr uint32_t kCodeProbes = 24;
+
+struct Palette {
+    uint32_t key[kCodes];
+    uint32_t over;
+};
+
+__device__ __forceinline__ uint32_t code_slot(uint32_t w) {
+    const uint32_t h = (w * 0x9E3779B1u) >> 24;
+    return h < 2u ? 2u : h;
+}
+__device__ __forceinline__ uint32_t next_slot(uint32_t slot) { return slot + 1u < kCodes ? slot + 1u : 2u; }
+
+// False when the map has no codes, or is known to have too many words for them.
+__device__ __forceinline__ bool palette_load(Palette& s, const DevMap& m) {
+    if (!m.codes) return false;
+    for (uint32_t k = threadIdx.x; k <= kCodes; k += blockDim.x) (k < kCodes ? s.key[k] : s.over) = m.palette[k];
+    __syncthreads();
+    return s.over == 0u;
+}
+
+__device__ __forceinline__ uint32_t find_code(Palette& s, const DevMap& m, uint32_t w) {
+    if (w == kSentinel) return 0u;
+    if (w == kGainOne) return 1u;
+    uint32_t slot = code_slot(w);
+    for (uint32_t n = 0; n < kCodeProbes && !s.over;) {
+        const uint32_t k = s.key[slot];
+        if (k == w) return slot;
+        if (k == kCodeFree) {
+            if ((threadIdx.x & 63u) == (uint32_t)__builtin_ctzll(__ballot(1))) {
+                const uint32_t old = atomicCAS(const_cast<uint32_t*>(m.palette) + slot, kCodeFree, w);
+                s.key[slot] = old == kCodeFree ? w : old;
+            }
+            continue;                            // look at the slot again
+        }
+        slot = next_slot(slot);
+        ++n;
+    }
+    s.over = 1u;
+    atomicOr(const_cast<uint32_t*>(m.palette) + kCodes, 1u);
+    return 0u;
+}
+
+// Starts the palette of a new encoding from kSampleCount voxels spread over
+// the grid: one workgroup, which reads them at once and enters their words in
+// LDS.  A map of many different probabilities overflows here, and its
+// encoding then spends nothing on codes.
+constexpr uint32_t kSampleThreads = 1024, kSampleEach = 4, kSampleCount = kSampleThreads * kSampleEach;
+
+__global__ __launch_bounds__(kSampleThreads) void palette_sample_kernel(const float* __restrict__ prob, DevMap m,
+                                                                        float occ_thr, float free_thr,
+                                                                        uint32_t* __restrict__ palette) {
+    __shared__ uint32_t s_key[kCodes];
+    __shared__ uint32_t s_over;
+    const uint32_t t = threadIdx.x;
+    if (t < kCodes) s_key[t] = t == 0u ? kSentinel : t == 1u ? kGainOne : kCodeFree;
+    if (t == 0u) s_over = 0u;
+    const uint64_t total = (uint64_t)m.nx * (uint64_t)m.ny * (uint64_t)m.nz;
+    float p[kSampleEach];
+#pragma unroll
+    for (uint32_t k = 0; k < kSampleEach; ++k) {
+        // a low-discrepancy walk over the grid (the golden ratio's multiples)
+        const uint32_t h = (k * kSampleThreads + t) * 0x9E3779B9u;
+        p[k] = prob[(uint64_t)h * total >> 32];
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t k = 0; k < kSampleEach; ++k) {
+        bool bad = false;
+        const uint32_t w = encode_prob(p[k], occ_thr, free_thr, bad);
+        if (w == kGainOne) continue;
+        uint32_t slot = code_slot(w), n = 0;
+        for (; n < kCodeProbes && !s_over; ++n) {
+            uint32_t old = s_key[slot];
+            if (old == kCodeFree) old = atomicCAS(&s_key[slot], kCodeFree, w);
+            if (old == kCodeFree || old == w) break;
+            slot = next_slot(slot);
+        }
+        if (n == kCodeProbes) s_over = 1u;
+    }
+    __syncthreads();
+    if (t < kCodes) palette[t] = s_key[t];
+    if (t == 0u) palette[kCodes] = s_over;
+}
+
 // Padded coordinates of stored word idx.
 __device__ __forceinline__ void word_coords(const DevMap& m, uint32_t idx, uint32_t& X, uint32_t& Y, uint32_t& Z) {
     if (m.tl == 0) {
@@ -59,6 +151,8 @@ __global__ __launch_bounds__(256) void encode_linear_kernel(const float* __restr
     const int X = (int)(blockIdx.x * 64u + (threadIdx.x & 63u));
     const int Y = (int)(blockIdx.y * 4u + (threadIdx.x >> 6));
     const int Z0 = (int)blockIdx.z * LAYERS;
+    __shared__ Palette s_pal;
+    const bool coded = palette_load(s_pal, m);
     if (X >= m.px || Y >= m.py) return;
     const bool xy = X > 0 && Y > 0 && X <= m.nx && Y <= m.ny;
     float p[LAYERS];
@@ -69,6 +163,7 @@ __global__ __launch_bounds__(256) void encode_linear_kernel(const float* __restr
                                         : 0.0f;
     }
     bool any_bad = false;
+    uint32_t known = kSentinel, code = 0u;       // the last word looked up
 #pragma unroll
     for (int k = 0; k < LAYERS; ++k) {
         const int Z = Z0 + k;
@@ -76,6 +171,11 @@ __global__ __launch_bounds__(256) void encode_linear_kernel(const float* __restr
         const bool in = xy && Z > 0 && Z <= m.nz;
         const uint32_t w = in ? encode_prob(p[k], occ_thr, free_thr, any_bad) : kSentinel;
         enc[((size_t)Z * m.py + (size_t)Y) * m.px + (size_t)X] = w;
+        if (coded) {
+            if (w != known) code = find_code(s_pal, m, known = w);
+            const_cast<uint8_t*>(m.codes)[code_offset(m.csy, m.csz, (uint32_t)X, (uint32_t)Y, (uint32_t)Z)] =
+                (uint8_t)code;
+        }
     }
     if (any_bad) atomicOr(bad, 1u);
 }
@@ -97,10 +197,13 @@ __global__ __launch_bounds__(256) void encode_column_kernel(const float* __restr
     const int px = (int)blockIdx.x * (64 / kRows) + lane % (64 / kRows), row = lane / (64 / kRows);
     const int tx = px / kCols, ty = (int)blockIdx.y;
     const int Z0 = ((int)blockIdx.z * 4 + wave) * LAYERS;
+    __shared__ Palette s_pal;
+    const bool coded = palette_load(s_pal, m);
     if (tx >= m.nbx) return;
     const int X = tx * T + (px % kCols) * 4, Y = ty * T + row;
     uint32_t* out = enc + ((size_t)(ty * m.nbx + tx) * m.pz << (2 * TL)) + row * T + (px % kCols) * 4;
     bool any_bad = false;
+    uint32_t known = kSentinel, code = 0u;       // the last word looked up
     float p[LAYERS][4];
     // the piece's voxels: four x of row Y, or for 2x2 tiles two x of rows Y and Y + 1
     auto at = [&](int e, int& x, int& y) {
@@ -118,10 +221,12 @@ __global__ __launch_bounds__(256) void encode_column_kernel(const float* __restr
             p[k][e] = at(e, x, y) && in_z ? prob[((size_t)z * m.ny + (size_t)y) * m.nx + (size_t)x] : 0.0f;
         }
     }
+    uint32_t codes[LAYERS];                      // the piece's four codes per layer
 #pragma unroll
     for (int k = 0; k < LAYERS; ++k) {
         const int Z = Z0 + k, z = Z - 1;
-        if (Z >= m.pz) break;
+        codes[k] = 0u;
+        if (Z >= m.pz) continue;
         const bool in_z = (unsigned)z < (unsigned)m.nz;
         uint32_t w[4];
 #pragma unroll
@@ -130,6 +235,41 @@ __global__ __launch_bounds__(256) void encode_column_kernel(const float* __restr
             w[e] = at(e, x, y) && in_z ? encode_prob(p[k][e], occ_thr, free_thr, any_bad) : kSentinel;
         }
         *reinterpret_cast<uint4*>(out + ((size_t)Z << (2 * TL))) = make_uint4(w[0], w[1], w[2], w[3]);
+        if (coded) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (w[e] != known) code = find_code(s_pal, m, known = w[e]);
+                codes[k] |= code << (8 * e);
+            }
+        }
+    }
+    if (coded) {
+        uint8_t* co = const_cast<uint8_t*>(m.codes);
+        auto place = [&](int y, int Z) { return co + code_offset(m.csy, m.csz, (uint32_t)X, (uint32_t)y, (uint32_t)Z); };
+        if constexpr (TL == 1) {
+            // two codes of each of two rows
+#pragma unroll
+            for (int k = 0; k < LAYERS; ++k) {
+                if (Z0 + k >= m.pz) break;
+                *reinterpret_cast<uint16_t*>(place(Y, Z0 + k)) = (uint16_t)codes[k];
+                *reinterpret_cast<uint16_t*>(place(Y + 1, Z0 + k)) = (uint16_t)(codes[k] >> 16);
+            }
+        } else if constexpr (LAYERS == 1) {
+            if (Z0 < m.pz) *reinterpret_cast<uint32_t*>(place(Y, Z0)) = codes[0];
+        } else {
+            // two rows of two layers are 16 consecutive codes: the lanes of a pair of
+            // rows exchange theirs and take every other pair of layers (the last
+            // one's second layer may lie in the padding of Z to whole blocks)
+#pragma unroll
+            for (int k = 0; k < LAYERS; k += 2) {
+                const uint32_t o0 = (uint32_t)__shfl_xor((int)codes[k], 64 / kRows, 64);
+                const uint32_t o1 = (uint32_t)__shfl_xor((int)codes[k + 1], 64 / kRows, 64);
+                const int odd = row & 1;
+                if (odd != (k / 2 & 1) || Z0 + k >= m.pz) continue;
+                *reinterpret_cast<uint4*>(place(Y - odd, Z0 + k)) =
+                    odd ? make_uint4(o0, codes[k], o1, codes[k + 1]) : make_uint4(codes[k], o0, codes[k + 1], o1);
+            }
+        }
     }
     if (any_bad) atomicOr(bad, 1u);
 }
@@ -175,6 +315,12 @@ static void launch_encode_column(const float* prob, uint32_t* enc, const DevMap&
 
 hipError_t launch_encode_map(const float* prob, uint32_t* enc, const DevMap& m, float occ_thr,
                              float free_thr, unsigned int* bad_flag, hipStream_t s) {
+    if (m.codes) {
+        hipLaunchKernelGGL(palette_sample_kernel, dim3(1), dim3(kSampleThreads), 0, s, prob, m, occ_thr, free_thr,
+                           const_cast<uint32_t*>(m.palette));
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     switch (m.tl) {
     case 1: launch_encode_column<1>(prob, enc, m, occ_thr, free_thr, bad_flag, s); break;
     case 2: launch_encode_column<2>(prob, enc, m, occ_thr, free_thr, bad_flag, s); break;

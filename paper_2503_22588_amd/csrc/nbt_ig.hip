@@ -210,6 +210,27 @@ uint64_t set_layout_geometry(DevMap& dm, int layout) {
     return (uint64_t)dm.nbx * dm.nby * (uint64_t)(T * T) * dm.pz;
 }
 
+// Maps have codes when their words take more than this (an XCD's L2).
+// Sets the code fields of dm (px, py, pz given) and returns the codes' size.
+// The fields of X and Y span powers of two, so a map takes up to 4 bytes of
+// codes per voxel, 69 MB for 256^3.
+constexpr size_t kCodesFrom = 4u << 20;
+static uint64_t set_code_geometry(DevMap& dm) {
+    auto bits = [](int n) {
+        int b = 3;
+        while ((1 << b) < n) ++b;
+        return b;
+    };
+    const int kx = bits(dm.px), ky = bits(dm.py), kz = bits(dm.pz);
+    dm.csy = 9 + kx - 3;
+    dm.csz = dm.csy + ky - 3;
+    if (dm.csz + kz - 3 > 31) return 0;
+    dm.mx = code_offset(dm.csy, dm.csz, (1u << kx) - 1u, 0, 0);
+    dm.my = code_offset(dm.csy, dm.csz, 0, (1u << ky) - 1u, 0);
+    dm.mz = code_offset(dm.csy, dm.csz, 0, 0, (1u << kz) - 1u);
+    return (uint64_t)((dm.pz + 7) / 8) << dm.csz;
+}
+
 }  // namespace nbt
 
 // ---------------------------------------------------------------- API -------
@@ -382,6 +403,21 @@ int nbt_ig_create_map(nbt_ig_ctx* ctx, const float* prob, int nx, int ny, int nz
     dm.nbx = geo.nbx; dm.nby = geo.nby;
     dm.inv_s = 1.0f / voxel_size;
     dm.ox = origin[0]; dm.oy = origin[1]; dm.oz = origin[2];
+    // The codes; a map that cannot have them is walked by its words, and so is
+    // one whose words fit an XCD's L2 anyway: its evaluations gain nothing
+    // (32 perspectives of 64x48 rays in a 64^3 map: 16 us by words, 17 by codes) and
+    // its encoding takes 3 us without and 9 with them.
+    const uint64_t bytes = set_code_geometry(dm);
+    if (bytes && map->enc_bytes > kCodesFrom) {
+        if (hipMalloc(&map->codes, bytes + (kCodes + 1) * 4) == hipSuccess) {
+            dm.codes = static_cast<const uint8_t*>(map->codes);
+            dm.palette = reinterpret_cast<const uint32_t*>(dm.codes + bytes);
+            dm.code_bytes = (uint32_t)bytes;
+        } else {
+            (void)hipGetLastError();
+            map->codes = nullptr;
+        }
+    }
 
     // Host or device source?  Host grids are staged through a device buffer.
     const size_t src_bytes = (size_t)nx * ny * nz * sizeof(float);
@@ -419,6 +455,7 @@ done:
     }
     if (rc != NBT_IG_OK) {
         (void)hipFree(map->enc);
+        if (map->codes) (void)hipFree(map->codes);
         if (map->bad) (void)hipFree(map->bad);
         delete map;
         return rc;
@@ -431,6 +468,7 @@ void nbt_ig_destroy_map(nbt_ig_map* map) {
     if (!map) return;
     DeviceGuard g(map->ctx->device);
     if (map->enc) (void)hipFree(map->enc);
+    if (map->codes) (void)hipFree(map->codes);
     if (map->bad) (void)hipFree(map->bad);
     map->enc = nullptr;
     delete map;
@@ -473,6 +511,26 @@ int nbt_ig_map_info(const nbt_ig_map* map, int* nx, int* ny, int* nz, float* vox
     return NBT_IG_OK;
 }
 
+// The default launch shape of a call whose rays are long (their longest is
+// some 100 voxels or more): a wave of a workgroup that ends early leaves its
+// place empty until the others have ended too, so single waves of one tile,
+// or of two where a perspective has many tiles (their sums are combined one
+// after the other) and the call has enough for the chip all the same.  Four
+// waves as balanced by resolve_launch -> now: 256 perspectives of 160x120
+// rays on a 256^3 table-top map 530 -> 501 us, 4096 of them 7.6 -> 7.26 ms,
+// 500 of 47x39 rays on a 320^3 map 331 -> 275 us.  The balanced shape stays where it
+// is faster: 64 of 160x120 rays 150 us (two tiles 174, one 200), 500 of 10x9
+// rays 43 (52), whose perspectives need no combining, and short rays (512 of
+// 64x48 rays of 45 voxels 74, single waves 76-83).
+static VpLaunch long_ray_launch(const DevMap& m, const CamParams& c, uint32_t n, const VpLaunch& L0) {
+    const double len = std::sqrt((double)c.dh * c.dh + (double)c.dv * c.dv + (double)c.range * c.range) * m.inv_s;
+    if (!(len >= 100.0) || std::max(m.nx, std::max(m.ny, m.nz)) < 100) return L0;
+    const uint32_t tiles = vp_tiles(c, 3);
+    if (tiles <= 8 || (tiles > 64 && (uint64_t)n * tiles < 40000)) return L0;
+    const VpLaunch L{1, 3, tiles > 64 ? 2 : 1, 0, 8};
+    return (uint64_t)n * vp_groups(c, L) * 64 < (1ull << 32) ? L : L0;
+}
+
 static int eval_viewpoints_impl(const nbt_ig_map* map, const nbt_ig_camera* cam, const float* poses,
                                 uint32_t n, float* ig_out, uint64_t* steps_out, nbt_ig_ray_digest* trace,
                                 void* stream, bool noalloc = false) {
@@ -482,10 +540,14 @@ static int eval_viewpoints_impl(const nbt_ig_map* map, const nbt_ig_camera* cam,
     if (n == 0) return NBT_IG_OK;
     if (!poses || !ig_out) return fail(NBT_IG_EINVAL, "poses or ig_out is NULL");
     nbt_ig_ctx* ctx = map->ctx;
-    const VpLaunch L = resolve_launch(c, ctx->vp_launch, n, ctx->cu_count);
-    // A launch shape that was set or tuned is kept; the default one walks the rays of a small call in segments.
+    VpLaunch L = resolve_launch(c, ctx->vp_launch, n, ctx->cu_count);
+    // A launch shape that was set or tuned is kept; in place of the default one
+    // the rays of a small call are walked in segments and long rays by single waves.
     SegLaunch seg{-1, 0, 0, 0, 0};
-    if (ctx->vp_launch == VpLaunch{}) seg = plan_segments(map->dm, c, n, ctx->cu_count);
+    if (ctx->vp_launch == VpLaunch{}) {
+        seg = plan_segments(map->dm, c, n, ctx->cu_count);
+        L = long_ray_launch(map->dm, c, n, L);
+    }
     const uint64_t groups = seg.segs_log2 > 0 ? seg.groups : vp_groups(c, L);
     if ((uint64_t)n * groups * (uint64_t)(L.waves * 64) >= (1ull << 32))
         return fail(NBT_IG_EUNSUPPORTED, "%u perspectives x %llu workgroups exceed the grid limit", n,

@@ -167,6 +167,17 @@ __device__ __forceinline__ int32_t offset_to_lin(const DevMap& m, uint32_t off) 
     return (z * m.ny + y) * m.nx + x;
 }
 
+// The same for the byte offset of a voxel's code (the inverse of code_offset).
+__device__ __forceinline__ int32_t code_to_lin(const DevMap& m, uint32_t off) {
+    const uint32_t X = (off & 3u) | (off >> 4 & 4u) | (off >> 9 & ((1u << (m.csy - 9)) - 1u)) << 3;
+    const uint32_t Y = (off >> 2 & 1u) | (off >> 3 & 2u) | (off >> 5 & 4u) |
+                       (off >> m.csy & ((1u << (m.csz - m.csy)) - 1u)) << 3;
+    const uint32_t Z = (off >> 3 & 1u) | (off >> 4 & 2u) | (off >> 6 & 4u) | (off >> m.csz) << 3;
+    const int x = (int)X - 1, y = (int)Y - 1, z = (int)Z - 1;
+    if (x < 0 || y < 0 || z < 0 || x >= m.nx || y >= m.ny || z >= m.nz) return -1;
+    return (z * m.ny + y) * m.nx + x;
+}
+
 // Parity mode of the throughput walks.  A walk instantiated with WalkTrace
 // keeps, beside each gather in flight, the byte offset it was issued for and
 // whether the generator was still inside the segment; every consumed visit
@@ -186,8 +197,10 @@ struct WalkTrace {
     // slot consumed while the lane is still walking: word x read at `off`,
     // `live` = the generator had not passed the segment end when it issued it
     __device__ __forceinline__ void consume(const DevMap& m, uint32_t x, uint32_t off, bool live, float t1) {
+        consume_at(x != kSentinel ? offset_to_lin(m, off) : -1, x, live, t1);
+    }
+    __device__ __forceinline__ void consume_at(int32_t lin, uint32_t x, bool live, float t1) {
         if (x != kSentinel) {
-            const int32_t lin = offset_to_lin(m, off);
             hash = fnv1a_u32(hash, (uint32_t)lin);
             gain += (double)__uint_as_float(x & ~kOccBit);
             ++steps;
@@ -453,6 +466,144 @@ __device__ __forceinline__ void walk_ray_pipelined(const DevMap& m, __amdgpu_buf
     acc += (double)part;
     if constexpr (COUNT) steps += n;
     if constexpr (traced<TR>()) tr->finish();
+}
+
+// One generator step of the code walk, for the lanes that execute it: past
+// gets the lanes whose next crossing lies beyond their segment's end t1; they
+// stay where they are.  The others step on the axis of that crossing (ties to
+// the lower axis): its t gains dt and its field of the offset g one.
+//
+// Compares and selects on lane masks issue at about half the rate of additions and
+// moves, so the three-way choice is made with the execution mask instead: the
+// lanes of one axis add their dt and fetch the axis' mask, then the next
+// axis' do.  The mask is what it was at the end.  17 VALU operations per
+// voxel with the sum and the palette, 24 in the word walk.
+__device__ __forceinline__ void code_step(float& tx, float& ty, float& tz, uint32_t& g, uint64_t& past, float t1,
+                                          uint32_t mx, uint32_t my, uint32_t mz, float dtx, float dty, float dtz) {
+    uint32_t mask, t;
+    uint64_t all, a, b;
+    asm("v_min3_f32 %[t], %[tx], %[ty], %[tz]\n\t"
+        "s_mov_b64 %[all], exec\n\t"
+        "v_cmp_gt_f32_e64 %[past], %[t], %[t1]\n\t"
+        "s_andn2_b64 exec, %[all], %[past]\n\t"
+        "s_mov_b64 %[b], exec\n\t"
+        "v_mov_b32_e32 %[mask], %[mz]\n\t"
+        "v_cmpx_eq_f32_e64 %[a], %[tx], %[t]\n\t"          // the lanes that step on x
+        "v_add_f32_e32 %[tx], %[tx], %[dtx]\n\t"
+        "v_mov_b32_e32 %[mask], %[mx]\n\t"
+        "s_andn2_b64 exec, %[b], %[a]\n\t"
+        "s_andn2_b64 %[b], %[b], %[a]\n\t"
+        "v_cmpx_eq_f32_e64 %[a], %[ty], %[t]\n\t"          // of the others, those on y
+        "v_add_f32_e32 %[ty], %[ty], %[dty]\n\t"
+        "v_mov_b32_e32 %[mask], %[my]\n\t"
+        "s_andn2_b64 exec, %[b], %[a]\n\t"                 // the rest on z
+        "v_add_f32_e32 %[tz], %[tz], %[dtz]\n\t"
+        "s_andn2_b64 exec, %[all], %[past]\n\t"
+        "v_bitop3_b32 %[t], %[g], %[mask], %[g] bitop3:0xf3\n\t"   // g | ~mask
+        "v_add_u32_e32 %[t], 1, %[t]\n\t"
+        "v_bfi_b32 %[g], %[mask], %[t], %[g]\n\t"
+        "s_mov_b64 exec, %[all]"
+        : [tx] "+v"(tx), [ty] "+v"(ty), [tz] "+v"(tz), [g] "+v"(g), [mask] "=&v"(mask), [t] "=&v"(t),
+          [all] "=&s"(all), [a] "=&s"(a), [b] "=&s"(b), [past] "=&s"(past)
+        : [t1] "v"(t1), [mx] "s"(mx), [my] "s"(my), [mz] "s"(mz), [dtx] "v"(dtx), [dty] "v"(dty), [dtz] "v"(dtz)
+        : "scc");
+}
+
+// The walk over a map's codes, software-pipelined as walk_ray_pipelined at
+// depth 8: the same visits, the same gains in the same order and runs, the same
+// 2^-149 where the IG-only walk meets the border.  pal: the map's palette in
+// LDS.  A code is looked up one slot before its word is used.
+//
+// The walk covers one stretch of a ray: from the state in `r`, which is that of
+// slot index K of the ray, it passes `skip` slots without visiting them and
+// then visits `groups` groups of kRunSlots slots, fewer when the ray ends (a
+// whole ray: K = skip = 0, and more groups than the map has voxels in a row).
+// K + skip is a multiple of kRunSlots, so the runs summed in binary32 are
+// those of the whole walk.  Returns whether the ray ended here: an Occupied
+// voxel, the border or the segment's end.
+template <bool COUNT, class TR = NoTrace>
+__device__ __forceinline__ bool walk_ray_codes(const DevMap& m, const uint32_t* pal, const RayState& r, uint32_t skip,
+                                               uint32_t groups, double& acc, uint32_t& steps, TR* tr = nullptr) {
+    constexpr int P = kRunSlots;
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc((void*)m.codes, (short)0, (int)m.code_bytes, 0x00020000);
+    const float dtx = r.dtx, dty = r.dty, dtz = r.dtz, t1 = r.t1;
+    const uint32_t mx = m.mx, my = m.my, mz = m.mz;
+    const uint32_t flip = (r.sx < 0 ? mx : 0u) | (r.sy < 0 ? my : 0u) | (r.sz < 0 ? mz : 0u);
+    uint32_t g = code_offset(m.csy, m.csz, (uint32_t)(r.ix + 1), (uint32_t)(r.iy + 1), (uint32_t)(r.iz + 1)) ^ flip;
+    float tx = r.tx, ty = r.ty, tz = r.tz;
+    auto load = [&] { return (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(rs, (int)(g ^ flip), 0, 0); };
+    bool refused = false;                        // the last slot passed already lay past the segment's end
+    for (; skip > 0; --skip) {
+        uint64_t ended;
+        code_step(tx, ty, tz, g, ended, t1, mx, my, mz, dtx, dty, dtz);
+        refused = __builtin_amdgcn_inverse_ballot_w64(ended);
+    }
+
+    uint32_t w[P];
+    uint64_t past[P];                            // per slot: lanes that had left their segment when it was issued
+    [[maybe_unused]] uint32_t wo[P];
+    w[0] = load();
+    past[0] = __ballot(refused);
+    if constexpr (traced<TR>()) wo[0] = g ^ flip;
+#pragma unroll
+    for (int u = 1; u < P; ++u) {
+        code_step(tx, ty, tz, g, past[u], t1, mx, my, mz, dtx, dty, dtz);
+        w[u] = load();
+        if constexpr (traced<TR>()) wo[u] = g ^ flip;
+    }
+    // the opaque zero keeps the codes 32 bits wide across the loop (else every
+    // group begins by waiting for its last gather to widen them)
+    uint32_t zero = 0;
+    asm volatile("" : "+s"(zero));
+#pragma unroll
+    for (int u = 0; u < P; ++u) w[u] += zero;
+
+    uint32_t n = 0;
+    uint64_t live = __ballot(true);              // lanes still walking
+    bool run = groups != 0u;
+    bool over = false;
+    uint32_t next = pal[w[0]];
+    while (run) {
+        float part = 0.0f;
+#pragma unroll
+        for (int u = 0; u < P; ++u) {
+            const uint32_t x = next;
+            const uint64_t gone = past[u];
+            [[maybe_unused]] uint32_t at;
+            if constexpr (traced<TR>()) at = wo[u];
+            code_step(tx, ty, tz, g, past[u], t1, mx, my, mz, dtx, dty, dtz);
+            w[u] = load();
+            if constexpr (traced<TR>()) wo[u] = g ^ flip;
+            next = pal[w[(u + 1) % P]];
+            if constexpr (traced<TR>()) {
+                if (__builtin_amdgcn_inverse_ballot_w64(live)) {
+                    const bool in = !__builtin_amdgcn_inverse_ballot_w64(gone);
+                    tr->consume_at(in && x != kSentinel ? code_to_lin(m, at) : -1, in ? x : kSentinel, in, t1);
+                }
+            }
+            // lanes past their segment's end stop; the others add the gain and
+            // stop at a set sign
+            uint64_t all, took;
+            asm volatile(
+                "s_mov_b64 %[all], exec\n\t"
+                "s_andn2_b64 %[took], %[live], %[gone]\n\t"
+                "s_and_b64 exec, %[all], %[took]\n\t"
+                "v_add_f32_e64 %[part], %[part], |%[x]|\n\t"
+                "v_cmpx_le_i32_e64 %[live], 0, %[x]\n\t"
+                "s_mov_b64 exec, %[all]\n\t"
+                "s_nop 1"                        // the new mask may be read as a VALU operand next
+                : [part] "+v"(part), [live] "+s"(live), [all] "=&s"(all), [took] "=&s"(took)
+                : [gone] "s"(gone), [x] "v"(x)
+                : "scc");
+            if constexpr (COUNT) n += __builtin_amdgcn_inverse_ballot_w64(took) && x != kSentinel ? 1u : 0u;
+        }
+        acc += (double)part;
+        over = !__builtin_amdgcn_inverse_ballot_w64(live);
+        run = !over && --groups != 0u;
+    }
+    if constexpr (COUNT) steps += n;
+    return over;
 }
 
 // walk_ray_pipelined over one stretch of a ray: starting at the state in `r`,

@@ -104,23 +104,32 @@ __device__ __forceinline__ void vp_combine(int waves, double acc, uint32_t steps
     }
 }
 
+// The map's palette in LDS (filled by the whole block), or nullptr when the
+// map is to be walked by its words.  The flag and the palette are requested
+// together.
+__device__ __forceinline__ const uint32_t* load_palette(const DevMap& m, uint32_t (&s_pal)[kCodes]) {
+    if (!m.codes) return nullptr;
+    const uint32_t over = m.palette[kCodes];
+    for (uint32_t k = 4u * threadIdx.x; k < kCodes; k += 4u * blockDim.x)
+        *reinterpret_cast<uint4*>(&s_pal[k]) = *reinterpret_cast<const uint4*>(m.palette + k);
+    __syncthreads();
+    return over == 0u ? s_pal : nullptr;
+}
+
 // The rays of workgroup-slice g of perspective vp: WAVES waves walk their
 // tiles, then the block's sum is written (groups == 1) or combined with the
 // other slices of the perspective (last slice writes).  Called uniformly by
 // the whole block.  TRACE (parity mode) also writes every ray's record to
 // trace[vp * N_E + k], built by the walk below from the offsets it gathers;
 // the walk and the IG arithmetic are those of the timed instance.
-template <int WAVES, int DEPTH, bool COUNT, bool TRACE>
+template <int WAVES, int DEPTH, bool COUNT, bool TRACE, bool CODED>
 __device__ __forceinline__ void vp_group(const DevMap& m, const CamParams& c,
-                                         const float* __restrict__ pp, uint32_t vp, uint32_t g,
+                                         const float (&pose)[12], uint32_t vp, uint32_t g,
                                          uint32_t groups, uint32_t tiles_x, uint32_t tiles,
                                          int tw_log2, int tpw, float* __restrict__ ig_out,
                                          unsigned long long* __restrict__ steps_out,
-                                         VpAccum* __restrict__ ws, nbt_ig_ray_digest* __restrict__ trace) {
-    float pose[12];
-#pragma unroll
-    for (int k = 0; k < 12; ++k) pose[k] = pp[k];
-
+                                         VpAccum* __restrict__ ws, nbt_ig_ray_digest* __restrict__ trace,
+                                         const uint32_t* pal) {
     const int wave = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
     const int tw = 1 << tw_log2;
@@ -162,11 +171,23 @@ __device__ __forceinline__ void vp_group(const DevMap& m, const CamParams& c,
                         else
                             walk_ray_pipelined<DEPTH, COUNT, TLv>(m, rs, ray, acc, steps);
                     };
-                    switch (m.tl) {          // the map's order; uniform per workgroup
-                    case 1: walk(std::integral_constant<int, 1>{}); break;
-                    case 2: walk(std::integral_constant<int, 2>{}); break;
-                    case 3: walk(std::integral_constant<int, 3>{}); break;
-                    default: walk(std::integral_constant<int, 0>{});
+                    bool coded = false;
+                    if constexpr (CODED) {
+                        if (pal) {           // uniform per workgroup
+                            coded = true;
+                            const uint32_t most = (uint32_t)(m.nx + m.ny + m.nz + 3) / kRunSlots + 2u;
+                            if constexpr (TRACE) walk_ray_codes<COUNT, WalkTrace>(m, pal, ray, 0u, most, acc, steps, &rec);
+                            else walk_ray_codes<COUNT>(m, pal, ray, 0u, most, acc, steps);
+                            if constexpr (TRACE) rec.finish();
+                        }
+                    }
+                    if (!coded) {
+                        switch (m.tl) {      // the map's order; uniform per workgroup
+                        case 1: walk(std::integral_constant<int, 1>{}); break;
+                        case 2: walk(std::integral_constant<int, 2>{}); break;
+                        case 3: walk(std::integral_constant<int, 3>{}); break;
+                        default: walk(std::integral_constant<int, 0>{});
+                        }
                     }
                 }
             } else if (st == kRayInvalid) {
@@ -180,7 +201,8 @@ __device__ __forceinline__ void vp_group(const DevMap& m, const CamParams& c,
     vp_combine<WAVES>(WAVES, acc, steps, invalid, vp, groups, (double)c.W * (double)c.H, ig_out, steps_out, ws);
 }
 
-template <int WAVES, int DEPTH, bool COUNT, bool TRACE>
+// CODED: the map has codes (walked by them unless its palette overflowed).
+template <int WAVES, int DEPTH, bool COUNT, bool TRACE, bool CODED>
 __global__ __launch_bounds__(WAVES * 64) void ig_viewpoints_kernel(
     DevMap m, CamParams c, const float* __restrict__ poses, uint32_t groups, uint32_t tiles_x,
     uint32_t tiles, int tw_log2, int tpw, int remap, float* __restrict__ ig_out,
@@ -189,8 +211,16 @@ __global__ __launch_bounds__(WAVES * 64) void ig_viewpoints_kernel(
     const uint32_t bid = remap > 0 ? xcd_logical(blockIdx.x, gridDim.x, (uint32_t)remap) : blockIdx.x;
     const uint32_t vp = bid / groups;
     const uint32_t g = bid - vp * groups;
-    vp_group<WAVES, DEPTH, COUNT, TRACE>(m, c, poses + 12 * (size_t)vp, vp, g, groups, tiles_x, tiles,
-                                         tw_log2, tpw, ig_out, steps_out, ws, trace);
+    float pose[12];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) pose[k] = poses[12 * (size_t)vp + k];
+    const uint32_t* pal = nullptr;
+    if constexpr (CODED) {
+        __shared__ __align__(16) uint32_t s_pal[kCodes];
+        pal = load_palette(m, s_pal);
+    }
+    vp_group<WAVES, DEPTH, COUNT, TRACE, CODED>(m, c, pose, vp, g, groups, tiles_x, tiles,
+                                         tw_log2, tpw, ig_out, steps_out, ws, trace, pal);
 }
 
 // Small calls: a ray's voxels are a serial chain (each step picks the next of
@@ -321,13 +351,18 @@ __global__ __launch_bounds__(kSegThreads) void ig_segments_kernel(DevMap m, CamP
 
     double acc = 0.0;
     uint32_t steps = 0;
+    __shared__ __align__(16) uint32_t s_pal[kCodes];
+    const uint32_t* pal = load_palette(m, s_pal);
     const __amdgpu_buffer_rsrc_t rs = map_rsrc(m);
     auto walk = [&](auto tl, auto* rec) {
         constexpr int TLv = decltype(tl)::value;
         using Rec = std::remove_pointer_t<decltype(rec)>;
         return walk_ray_stretch<COUNT, TLv, Rec>(m, rs, ray, first * kRunSlots - slot, next - first, acc, steps, rec);
     };
-    auto walk_order = [&](auto* rec) {           // the map's order; uniform per workgroup
+    auto walk_order = [&](auto* rec) {           // codes or the map's order; uniform per workgroup
+        using Rec = std::remove_pointer_t<decltype(rec)>;
+        if (pal)
+            return walk_ray_codes<COUNT, Rec>(m, pal, ray, first * kRunSlots - slot, next - first, acc, steps, rec);
         switch (m.tl) {
         case 1: return walk(std::integral_constant<int, 1>{}, rec);
         case 2: return walk(std::integral_constant<int, 2>{}, rec);
@@ -373,8 +408,10 @@ __global__ __launch_bounds__(kSegThreads) void ig_segments_kernel(DevMap m, CamP
 // map-major order; each workgroup pops items from an atomic counter until
 // the queue is empty, so uneven maps and perspective counts balance across
 // the chip and co-resident workgroups share one map in L2.
-template <int WAVES, int DEPTH, bool COUNT>
-__global__ __launch_bounds__(WAVES * 64) void ig_batch_kernel(
+// Seven waves per SIMD: left to itself the coded kernel takes 98 VGPRs (five
+// waves; 64 maps 2.9 ms against 2.55).
+template <int WAVES, int DEPTH, bool COUNT, bool CODED>
+__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(CODED ? 7 : 1, CODED ? 7 : 8))) void ig_batch_kernel(
     const DevMap* __restrict__ maps, uint32_t n_maps, const uint32_t* __restrict__ offsets,
     uint32_t capacity, CamParams c, const float* __restrict__ poses, uint32_t groups,
     uint32_t tiles_x, uint32_t tiles, int tw_log2, int tpw, unsigned int* __restrict__ queue,
@@ -384,6 +421,8 @@ __global__ __launch_bounds__(WAVES * 64) void ig_batch_kernel(
     uint32_t total = offsets[n_maps];
     total = total < capacity ? total : capacity;
     const uint64_t items = (uint64_t)total * groups;
+    const uint32_t* pal = nullptr;
+    uint32_t pal_map = n_maps;              // the map whose palette is loaded
     for (;;) {
         __syncthreads();                    // previous item's reductions are done
         if (threadIdx.x == 0) {
@@ -407,8 +446,18 @@ __global__ __launch_bounds__(WAVES * 64) void ig_batch_kernel(
         const uint32_t vp = it / groups;
         const uint32_t g = it - vp * groups;
         const DevMap m = maps[s_map];
-        vp_group<WAVES, DEPTH, COUNT, false>(m, c, poses + 12 * (size_t)vp, vp, g, groups, tiles_x, tiles,
-                                             tw_log2, tpw, ig_out, steps_out, ws, nullptr);
+        float pose[12];
+#pragma unroll
+        for (int k = 0; k < 12; ++k) pose[k] = poses[12 * (size_t)vp + k];
+        if constexpr (CODED) {
+            __shared__ __align__(16) uint32_t s_pal[kCodes];
+            if (s_map != pal_map) {         // (the barriers above: nobody reads the old one)
+                pal_map = s_map;
+                pal = load_palette(m, s_pal);
+            }
+        }
+        vp_group<WAVES, DEPTH, COUNT, false, CODED>(m, c, pose, vp, g, groups, tiles_x, tiles,
+                                             tw_log2, tpw, ig_out, steps_out, ws, nullptr, pal);
     }
 }
 
@@ -519,11 +568,15 @@ hipError_t launch_eval_viewpoints(const DevMap& m, const CamParams& c, const flo
     };
     // Without steps_out the walk skips the per-voxel visit count.
     const bool count = steps_out != nullptr;
+    // Only the walk at the default depth knows codes.
+    const bool coded = m.codes != nullptr && L.depth == 8;
 #define NBT_VP_GO(W, D)                                                                            \
-    (trace ? (count ? go(ig_viewpoints_kernel<W, D, true, true>, W)                                \
-                    : go(ig_viewpoints_kernel<W, D, false, true>, W))                              \
-           : (count ? go(ig_viewpoints_kernel<W, D, true, false>, W)                               \
-                    : go(ig_viewpoints_kernel<W, D, false, false>, W)))
+    (coded ? NBT_VP_GO2(W, D, (D == 8)) : NBT_VP_GO2(W, D, false))
+#define NBT_VP_GO2(W, D, CD)                                                                       \
+    (trace ? (count ? go(ig_viewpoints_kernel<W, D, true, true, CD>, W)                            \
+                    : go(ig_viewpoints_kernel<W, D, false, true, CD>, W))                          \
+           : (count ? go(ig_viewpoints_kernel<W, D, true, false, CD>, W)                           \
+                    : go(ig_viewpoints_kernel<W, D, false, false, CD>, W)))
 #define NBT_VP_DEPTHS(W)                                  \
     case W:                                               \
         switch (L.depth) {                                \
@@ -543,6 +596,7 @@ hipError_t launch_eval_viewpoints(const DevMap& m, const CamParams& c, const flo
             return hipErrorInvalidValue;
     }
 #undef NBT_VP_GO
+#undef NBT_VP_GO2
 #undef NBT_VP_DEPTHS
     return hipGetLastError();
 }
@@ -607,10 +661,15 @@ hipError_t launch_eval_segments(const DevMap& m, const CamParams& c, const float
     return hipGetLastError();
 }
 
-const void* batch_kernel_ptr(int waves, int depth, bool count) {
-#define NBT_BK(W, D)                                                                      \
-    if (waves == W && depth == D)                                                         \
-        return count ? (const void*)ig_batch_kernel<W, D, true> : (const void*)ig_batch_kernel<W, D, false>;
+const void* batch_kernel_ptr(int waves, int depth, bool count, bool coded) {
+#define NBT_BK(W, D)                                                                               \
+    if (waves == W && depth == D) {                                                                \
+        if (coded && D == 8)                                                                       \
+            return count ? (const void*)ig_batch_kernel<W, D, true, D == 8>                        \
+                         : (const void*)ig_batch_kernel<W, D, false, D == 8>;                      \
+        return count ? (const void*)ig_batch_kernel<W, D, true, false>                             \
+                     : (const void*)ig_batch_kernel<W, D, false, false>;                           \
+    }
     NBT_BK(1, 1) NBT_BK(1, 2) NBT_BK(1, 4) NBT_BK(1, 8)
     NBT_BK(2, 1) NBT_BK(2, 2) NBT_BK(2, 4) NBT_BK(2, 8)
     NBT_BK(4, 1) NBT_BK(4, 2) NBT_BK(4, 4) NBT_BK(4, 8)
