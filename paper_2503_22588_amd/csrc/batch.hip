@@ -40,7 +40,9 @@ int set_batch_launch(nbt_ig_batch* b, const VpLaunch& L) {
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, L.waves * 64, 0);
     if (e != hipSuccess) return hip_fail(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
     if (per_cu < 1) per_cu = 1;
-    b->launch = resolve_launch(b->cam, L);
+    // split for the perspectives a run may have, as a call of that many would be
+    // (3 maps with 202 perspectives of 41x41 rays 114 -> 66 us, 4 with 740 of 64x44 196 -> 153)
+    b->launch = resolve_launch(b->cam, L, b->capacity, b->ctx->cu_count);
     b->grid = (uint32_t)(per_cu * b->ctx->cu_count);
     drop_graph(b);
     return NBT_IG_OK;
