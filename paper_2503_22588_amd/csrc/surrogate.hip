@@ -762,16 +762,53 @@ __global__ __launch_bounds__(kSelThreads) void select_stage_kernel(const float* 
     }
 }
 
+// Keys order candidates by value (descending) and index (ascending on ties):
+// mono_key(value) << 32 | ~index.  NaN ranks below everything.
+__device__ __forceinline__ unsigned long long rank_key(float v, uint32_t idx) {
+    return ((unsigned long long)mono_key(v) << 32) | (unsigned long long)(0xFFFFFFFFu - idx);
+}
+
+// Thread i < kr holds candidate `idx` of value `v`: the k best are written
+// best first, ties to the lower index.  Keys are distinct (the index is in the
+// low word), so a candidate's rank is the number of larger keys.  s_key holds
+// kMaxRescore + 2 keys.  Called by the whole block.
+__device__ __forceinline__ void rank_and_write(unsigned long long* s_key, float v, uint32_t idx, uint32_t kr,
+                                               uint32_t k, uint32_t* __restrict__ idx_out,
+                                               float* __restrict__ val_out) {
+    const uint32_t i = threadIdx.x;
+    const unsigned long long key = i < kr ? rank_key(v, idx) : 0ull;
+    if (i < kr) s_key[i] = key;
+    if (i == 0 && (kr & 1u)) s_key[kr] = 0ull;       // pads an odd count: ranks above no key
+    __syncthreads();
+    if (i >= kr) return;
+    uint32_t rank = 0;
+    const ulonglong2* kp = reinterpret_cast<const ulonglong2*>(s_key);
+#pragma unroll 4
+    for (uint32_t j = 0; j < (kr + 1) / 2; ++j) {
+        const ulonglong2 kk = kp[j];
+        rank += (kk.x > key ? 1u : 0u) + (kk.y > key ? 1u : 0u);
+    }
+    if (rank < k) {
+        idx_out[rank] = idx;
+        if (val_out) val_out[rank] = v;
+    }
+}
+
 // The last stage (one workgroup, count <= 1024 R): the k best become the
-// candidates, with their poses when `poses` is given.
-template <bool FROM_PRED, int R>
+// candidates, with their poses when `poses` is given.  ORDER (top-k): they
+// come out in order with their values (from `vals`) instead, where a launch
+// of its own for the order took 5 us (top 256 of 65,536: 20.5 us in three launches,
+// 18.3 in two; top 10 of 4,096: 9.3, 8.1 in one).
+template <bool FROM_PRED, int R, bool ORDER>
 __global__ __launch_bounds__(kSelThreads) void select_final_kernel(const float* __restrict__ pred,
                                                                    const uint32_t* __restrict__ in_key,
                                                                    const uint32_t* __restrict__ in_idx,
                                                                    uint32_t count, uint32_t k,
                                                                    const float* __restrict__ poses,
                                                                    uint32_t* __restrict__ cand,
-                                                                   float* __restrict__ cand_poses) {
+                                                                   float* __restrict__ cand_poses,
+                                                                   const float* __restrict__ vals,
+                                                                   float* __restrict__ val_out) {
     __shared__ uint32_t s_hist[4096];
     __shared__ uint32_t s_wave[kSelThreads / 64];
     __shared__ uint32_t s_red[3 * (kSelThreads / 64)];
@@ -802,6 +839,12 @@ __global__ __launch_bounds__(kSelThreads) void select_final_kernel(const float* 
     });
     __syncthreads();
     const uint32_t got = min(s_count, k);
+    if constexpr (ORDER) {
+        __shared__ __align__(16) unsigned long long s_key[kMaxRescore + 2];
+        const uint32_t idx_t = t < got ? s_cand[t] : 0u;
+        rank_and_write(s_key, t < got ? vals[idx_t] : 0.0f, idx_t, got, k, cand, val_out);
+        return;
+    }
     for (uint32_t p = t; p < got; p += kSelThreads) cand[p] = s_cand[p];
     if (poses) {
         for (uint32_t j = t; j < 12u * got; j += kSelThreads) {
@@ -811,46 +854,18 @@ __global__ __launch_bounds__(kSelThreads) void select_final_kernel(const float* 
     }
 }
 
-// ---------------------------------------------------------------- top-k ----
-// Keys order candidates by value (descending) and index (ascending on ties):
-// mono_key(value) << 32 | ~index.  NaN ranks below everything.
-__device__ __forceinline__ unsigned long long rank_key(float v, uint32_t idx) {
-    return ((unsigned long long)mono_key(v) << 32) | (unsigned long long)(0xFFFFFFFFu - idx);
-}
-
-// Final pick among the rescored candidates, and the order of a top-k set:
-// slot j holds candidate cand[j] with value vals[j] (vals[cand[j]] when
-// `gather`); the k best come out best first, ties to the lower candidate
-// index.  Keys are distinct (the candidate index is in the low word), so each
-// slot's rank is the number of larger keys, and the k best write themselves.
+// ---------------------------------------------------------------- final pick ----
+// Final pick among the rescored candidates: slot j holds candidate cand[j]
+// with value vals[j]; the k best come out best first, ties to the lower
+// candidate index.
 __global__ __launch_bounds__(kMaxRescore) void final_select_kernel(const float* __restrict__ vals,
                                                                    const uint32_t* __restrict__ cand,
-                                                                   uint32_t kr, uint32_t k, int gather,
+                                                                   uint32_t kr, uint32_t k,
                                                                    uint32_t* __restrict__ idx_out,
                                                                    float* __restrict__ val_out) {
     __shared__ __align__(16) unsigned long long s_key[kMaxRescore + 2];
     const uint32_t i = threadIdx.x;
-    unsigned long long key = 0ull;
-    float v = 0.0f;
-    if (i < kr) {
-        v = gather ? vals[cand[i]] : vals[i];
-        key = rank_key(v, cand[i]);
-        s_key[i] = key;
-    }
-    if (i == 0 && (kr & 1u)) s_key[kr] = 0ull;       // pads an odd count: ranks above no key
-    __syncthreads();
-    if (i >= kr) return;
-    uint32_t rank = 0;
-    const ulonglong2* kp = reinterpret_cast<const ulonglong2*>(s_key);
-#pragma unroll 4
-    for (uint32_t j = 0; j < (kr + 1) / 2; ++j) {
-        const ulonglong2 kk = kp[j];
-        rank += (kk.x > key ? 1u : 0u) + (kk.y > key ? 1u : 0u);
-    }
-    if (rank < k) {
-        idx_out[rank] = cand[i];
-        if (val_out) val_out[rank] = v;
-    }
+    rank_and_write(s_key, i < kr ? vals[i] : 0.0f, i < kr ? cand[i] : 0u, kr, k, idx_out, val_out);
 }
 
 // ---------------------------------------------------------------- launchers
@@ -907,7 +922,8 @@ size_t select_scratch_items(uint32_t n, uint32_t k) {
 }
 
 hipError_t launch_select(const float* pred, uint32_t n, uint32_t k, const float* poses, uint32_t* scratch,
-                         size_t scratch_items, uint32_t* cand, float* cand_poses, hipStream_t s) {
+                         size_t scratch_items, uint32_t* cand, float* cand_poses, bool order, float* val_out,
+                         hipStream_t s) {
     const uint32_t* in_key = nullptr;
     const uint32_t* in_idx = nullptr;
     uint32_t count = n;
@@ -930,22 +946,26 @@ hipError_t launch_select(const float* pred, uint32_t n, uint32_t k, const float*
         flip ^= 1;
     }
     // four items per thread when they fit, sixteen otherwise
+#define NBT_FINAL2(FP, RR, O)                                                                            \
+    hipLaunchKernelGGL((select_final_kernel<FP, RR, O>), dim3(1), dim3(kSelThreads), 0, s, FP ? pred : nullptr, \
+                       in_key, in_idx, count, k, poses, cand, cand_poses, pred, val_out)
 #define NBT_FINAL(FP, RR)                                                                                \
-    hipLaunchKernelGGL((select_final_kernel<FP, RR>), dim3(1), dim3(kSelThreads), 0, s, FP ? pred : nullptr, \
-                       in_key, in_idx, count, k, poses, cand, cand_poses)
+    do {                                                                                                 \
+        if (order) NBT_FINAL2(FP, RR, true); else NBT_FINAL2(FP, RR, false);                             \
+    } while (0)
     if (!in_key) {
         if (count <= 4 * kSelThreads) NBT_FINAL(true, 4); else NBT_FINAL(true, 16);
     } else {
         if (count <= 4 * kSelThreads) NBT_FINAL(false, 4); else NBT_FINAL(false, 16);
     }
 #undef NBT_FINAL
+#undef NBT_FINAL2
     return hipGetLastError();
 }
 
-hipError_t launch_final_select(const float* vals, const uint32_t* cand, uint32_t kr, uint32_t k, bool gather,
-                               uint32_t* idx_out, float* val_out, hipStream_t s) {
-    hipLaunchKernelGGL(final_select_kernel, dim3(1), dim3(kMaxRescore), 0, s, vals, cand, kr, k, gather ? 1 : 0,
-                       idx_out, val_out);
+hipError_t launch_final_select(const float* vals, const uint32_t* cand, uint32_t kr, uint32_t k, uint32_t* idx_out,
+                               float* val_out, hipStream_t s) {
+    hipLaunchKernelGGL(final_select_kernel, dim3(1), dim3(kMaxRescore), 0, s, vals, cand, kr, k, idx_out, val_out);
     return hipGetLastError();
 }
 

@@ -48,14 +48,16 @@ hipError_t launch_mlp(const float* poses, uint32_t n, const float poi[3], float 
 // Items one stage buffer of launch_select holds for n predictions (0: one
 // workgroup takes them all); its scratch is 4 x that many uint32.
 size_t select_scratch_items(uint32_t n, uint32_t k);
-// The k best predictions (ties to the lower index) as a set, with their poses.
+// The k best predictions (ties to the lower index) in cand: as a set, with their
+// poses when `poses` is given, or (order) best first, with their values in
+// val_out (may be NULL).
 hipError_t launch_select(const float* pred, uint32_t n, uint32_t k, const float* poses, uint32_t* scratch,
-                         size_t scratch_items, uint32_t* cand, float* cand_poses, hipStream_t s);
-// The k best of kr slots (slot j: candidate cand[j], value vals[j], or
-// vals[cand[j]] when gather), best first, ties to the lower candidate index;
-// val_out may be NULL.  kr <= kMaxRescore.
-hipError_t launch_final_select(const float* vals, const uint32_t* cand, uint32_t kr, uint32_t k, bool gather,
-                               uint32_t* idx_out, float* val_out, hipStream_t s);
+                         size_t scratch_items, uint32_t* cand, float* cand_poses, bool order, float* val_out,
+                         hipStream_t s);
+// The k best of kr slots (slot j: candidate cand[j] of value vals[j]), best
+// first, ties to the lower candidate index; val_out may be NULL.  kr <= kMaxRescore.
+hipError_t launch_final_select(const float* vals, const uint32_t* cand, uint32_t kr, uint32_t k, uint32_t* idx_out,
+                               float* val_out, hipStream_t s);
 hipError_t launch_bf16_to_f32(const __bf16* in, uint32_t n, float* out, hipStream_t s);
 
 }  // namespace nbt

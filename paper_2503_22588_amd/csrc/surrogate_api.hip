@@ -279,11 +279,11 @@ int nbt_ig_surrogate_select(nbt_ig_surrogate* s, const nbt_ig_map* map, const nb
                               s->b3, s->out_scale, s->pred, s->ctx->cu_count, st);
     if (e == hipSuccess)
         e = launch_select(s->pred, n, k_rescore, poses, s->sel, select_scratch_items(n, k_rescore), s->cand,
-                          s->cand_poses, st);
+                          s->cand_poses, false, nullptr, st);
     if (e != hipSuccess) return hip_fail(e, "surrogate mlp and selection");
     if (int rc = nbt_ig_eval_viewpoints(map, cam, s->cand_poses, k_rescore, s->cand_ig, nullptr, stream))
         return rc;
-    e = launch_final_select(s->cand_ig, s->cand, k_rescore, k, false, idx_out, ig_out, st);
+    e = launch_final_select(s->cand_ig, s->cand, k_rescore, k, idx_out, ig_out, st);
     if (e != hipSuccess) return hip_fail(e, "surrogate select");
     return NBT_IG_OK;
 }
@@ -313,19 +313,17 @@ int nbt_ig_top_k(nbt_ig_ctx* ctx, const float* values, uint32_t n, uint32_t k, u
     DeviceGuard g(ctx->device);
     if (!g.ok) return fail(NBT_IG_EDEVICE, "cannot select device %d", ctx->device);
     hipStream_t st = (hipStream_t)stream;
-    // the radix selection's stage buffers, then the chosen set (k indices)
-    const size_t items = select_scratch_items(n, k);
-    const size_t need = (4 * items + k) * sizeof(uint32_t);
-    {
+    const size_t items = select_scratch_items(n, k);          // the radix selection's stage buffers
+    if (items) {
         std::lock_guard<std::mutex> lk(ctx->mu);
         void* p = ctx->topk_keep;
-        if (int rc = grow_buffer(&p, &ctx->topk_bytes, &ctx->topk_async, need, st, "top-k scratch")) return rc;
+        if (int rc = grow_buffer(&p, &ctx->topk_bytes, &ctx->topk_async, 4 * items * sizeof(uint32_t), st,
+                                 "top-k scratch"))
+            return rc;
         ctx->topk_keep = static_cast<unsigned long long*>(p);
     }
-    uint32_t* scratch = reinterpret_cast<uint32_t*>(ctx->topk_keep);
-    uint32_t* set = scratch + 4 * items;
-    hipError_t e = launch_select(values, n, k, nullptr, scratch, items, set, nullptr, st);
-    if (e == hipSuccess) e = launch_final_select(values, set, k, k, true, idx_out, val_out, st);
+    const hipError_t e = launch_select(values, n, k, nullptr, reinterpret_cast<uint32_t*>(ctx->topk_keep), items,
+                                       idx_out, nullptr, true, val_out, st);
     if (e != hipSuccess) return hip_fail(e, "top-k");
     return NBT_IG_OK;
 }
