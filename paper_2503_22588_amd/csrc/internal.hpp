@@ -222,7 +222,7 @@ const void* batch_reset_ptr();
 hipError_t launch_eval_cost(const float* id_pos, const float* id_ig, uint32_t nb, uint32_t np, float p,
                             const float* poses, uint32_t h, uint32_t k, const float poi[3], float tan_h,
                             float tan_v, float w_i, float eps, float* g_out, float* o_out, float* cost,
-                            hipStream_t s);
+                            int cu_count, hipStream_t s);
 
 // Number of workgroups a perspective is split into for a launch shape.
 // Raises a kernel's dynamic-LDS limit to `bytes` on the current device when

@@ -791,7 +791,7 @@ int nbt_ig_eval_cost(nbt_ig_ctx* ctx, const float* id_pos, const float* id_ig, u
     DeviceGuard g(ctx->device);
     if (!g.ok) return fail(NBT_IG_EDEVICE, "cannot select device %d", ctx->device);
     hipError_t e = launch_eval_cost(id_pos, id_ig, n_ids, n_persp, p, poses, n_horizons, steps, poi,
-                                    tan_half_fov_h, tan_half_fov_v, w_i, eps, g_out, o_out, cost_out,
+                                    tan_half_fov_h, tan_half_fov_v, w_i, eps, g_out, o_out, cost_out, ctx->cu_count,
                                     (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "idw_query_kernel");
     return NBT_IG_OK;

@@ -1,7 +1,7 @@
 """GPU check of the planner's cost terms at the edges of the kernel's split: horizons of one
 state, exactly a workgroup's tile, one more than it and longer than a tile (their cost is then
-summed by a launch of its own), and perspective counts below, at and beside the waves' shares
-and scalar-load blocks, against the float64 reference."""
+summed by a launch of its own), and perspective counts below, at and beside the waves' shares,
+the scalar-load blocks and the LDS chunks, with one horizon to a workgroup and with several, against the float64 reference."""
 
 import math
 
@@ -16,7 +16,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("p", [2.0, 0.7])
 @pytest.mark.parametrize("h,k,nb,npp", [(1, 1, 1, 1), (7, 1, 2, 15), (3, 20, 1, 16), (5, 21, 3, 129), (2, 63, 17, 8),
-                                        (3, 64, 2, 130), (2, 65, 2, 1025), (1, 100, 33, 7)])
+                                        (3, 64, 2, 130), (2, 65, 2, 1025), (1, 100, 33, 7),
+                                        (4, 32, 2, 1024), (2, 33, 2, 47), (3, 13, 2, 2500), (300, 60, 1, 40)])
 def test_cost_terms_at_tile_edges(h, k, nb, npp, p):
     import torch
     if not torch.cuda.is_available():
@@ -34,7 +35,7 @@ def test_cost_terms_at_tile_edges(h, k, nb, npp, p):
     dev = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
     G, O, cost = nbt.eval_cost(ctx, dev(id_pos), dev(id_ig), dev(poses), poi, tan_h, tan_v, p=p, w_i=25.0)
     torch.cuda.synchronize()
-    for i in range(h):
+    for i in range(0, h, 1 + h // 20):
         g, o, c = I.horizon_cost(poses[i].astype(np.float64), poi.astype(np.float64), tan_h, tan_v,
                                  id_pos.astype(np.float64), id_ig.astype(np.float64), p=p, w_i=25.0)
         assert np.max(np.abs(G[i].cpu().numpy() - g) / g) <= 1e-5
