@@ -71,6 +71,62 @@ __device__ __forceinline__ void dda_advance_idx(float& tx, float& ty, float& tz,
     alive = go;
 }
 
+// dda_advance_idx for the linear order, for the lanes that execute it.  The
+// three-way choice is made with the execution mask, as in code_step: the
+// lanes of one axis add its dt, map stride and bitset stride, then the next
+// axis' do; lanes past their segment's end t1 are sent to the corner
+// sentinel and stay there.  14 VALU operations, four of them compares, where
+// the selects made 15 of which ten issue at half rate.  `past`: those lanes.
+__device__ __forceinline__ void linear_step_idx(float& tx, float& ty, float& tz, uint32_t& off, int& idx,
+                                                uint64_t& past, float t1, int dxo, int dyo, int dzo, int dbx, int dby,
+                                                int dbz, float dtx, float dty, float dtz) {
+    float t;
+    uint64_t all, a, b;
+    asm("v_min3_f32 %[t], %[tx], %[ty], %[tz]\n\t"
+        "s_mov_b64 %[all], exec\n\t"
+        "v_cmp_gt_f32_e64 %[past], %[t], %[t1]\n\t"
+        "s_and_b64 exec, %[all], %[past]\n\t"
+        "v_mov_b32_e32 %[off], 0\n\t"
+        "s_andn2_b64 exec, %[all], %[past]\n\t"
+        "s_mov_b64 %[b], exec\n\t"
+        "v_cmpx_eq_f32_e64 %[a], %[tx], %[t]\n\t"          // the lanes that step on x
+        "v_add_f32_e32 %[tx], %[tx], %[dtx]\n\t"
+        "v_add_u32_e32 %[off], %[off], %[dxo]\n\t"
+        "v_add_u32_e32 %[idx], %[idx], %[dbx]\n\t"
+        "s_andn2_b64 exec, %[b], %[a]\n\t"
+        "s_andn2_b64 %[b], %[b], %[a]\n\t"
+        "v_cmpx_eq_f32_e64 %[a], %[ty], %[t]\n\t"          // of the others, those on y
+        "v_add_f32_e32 %[ty], %[ty], %[dty]\n\t"
+        "v_add_u32_e32 %[off], %[off], %[dyo]\n\t"
+        "v_add_u32_e32 %[idx], %[idx], %[dby]\n\t"
+        "s_andn2_b64 exec, %[b], %[a]\n\t"                 // the rest on z
+        "v_add_f32_e32 %[tz], %[tz], %[dtz]\n\t"
+        "v_add_u32_e32 %[off], %[off], %[dzo]\n\t"
+        "v_add_u32_e32 %[idx], %[idx], %[dbz]\n\t"
+        "s_mov_b64 exec, %[all]\n\t"
+        "s_nop 1"                                            // past may be read as a VALU operand next
+        : [tx] "+v"(tx), [ty] "+v"(ty), [tz] "+v"(tz), [off] "+v"(off), [idx] "+v"(idx), [t] "=&v"(t),
+          [all] "=&s"(all), [a] "=&s"(a), [b] "=&s"(b), [past] "=&s"(past)
+        : [t1] "v"(t1), [dxo] "v"(dxo), [dyo] "v"(dyo), [dzo] "v"(dzo), [dbx] "v"(dbx), [dby] "v"(dby),
+          [dbz] "v"(dbz), [dtx] "v"(dtx), [dty] "v"(dty), [dtz] "v"(dtz)
+        : "scc");
+}
+
+// One generator step of the union walk.  alive: still inside the segment.
+template <int TL, bool ALIVE>
+__device__ __forceinline__ void union_advance(float& tx, float& ty, float& tz, uint32_t& off, int& idx, bool& alive,
+                                              float t1, const OffsetSteps& o, int dbx, int dby, int dbz, float dtx,
+                                              float dty, float dtz) {
+    if constexpr (TL == 0) {
+        uint64_t past;
+        linear_step_idx(tx, ty, tz, off, idx, past, t1, o.dx, o.dy, o.dz, dbx, dby, dbz, dtx, dty, dtz);
+        if constexpr (ALIVE) alive = !__builtin_amdgcn_inverse_ballot_w64(past);
+    } else {
+        dda_advance_idx<TL>(tx, ty, tz, off, idx, alive, t1, o.dx, o.dy, o.dz, o.bigx, o.bigy, o.flip, dbx, dby, dbz,
+                            dtx, dty, dtz);
+    }
+}
+
 // Pipelined walk that also sets, in the LDS bitset `bits`, the bit of every
 // visited voxel whose box position ((z-lz)*ay + (y-ly))*ax + (x-lx), minus
 // `base`, lies in [0, nbits): the slice of the box one pass of the union
@@ -120,8 +176,7 @@ __device__ __forceinline__ uint32_t walk_ray_mark(const DevMap& m, __amdgpu_buff
     }
 #pragma unroll
     for (int u = 1; u < P; ++u) {
-        dda_advance_idx<TL>(tx, ty, tz, off, bidx, alive, t1, o.dx, o.dy, o.dz, o.bigx, o.bigy, o.flip,
-                               dbx, dby, dbz, dtx, dty, dtz);
+        union_advance<TL, traced<TR>()>(tx, ty, tz, off, bidx, alive, t1, o, dbx, dby, dbz, dtx, dty, dtz);
         w[u] = load_word(rs, off);
         bi[u] = bidx;
         if constexpr (traced<TR>()) {
@@ -156,8 +211,7 @@ __device__ __forceinline__ uint32_t walk_ray_mark(const DevMap& m, __amdgpu_buff
                 }
             }
             run = run && (int)x >= 0;
-            dda_advance_idx<TL>(tx, ty, tz, off, bidx, alive, t1, o.dx, o.dy, o.dz, o.bigx, o.bigy, o.flip,
-                               dbx, dby, dbz, dtx, dty, dtz);
+            union_advance<TL, traced<TR>()>(tx, ty, tz, off, bidx, alive, t1, o, dbx, dby, dbz, dtx, dty, dtz);
             w[u] = load_word(rs, off);
             bi[u] = bidx;
             if constexpr (traced<TR>()) {
@@ -277,6 +331,9 @@ __global__ __launch_bounds__(256) void traj_box_kernel(DevMap m, CamParams c,
 // the box's positions.  The epilogue of every pass hands word w of the whole
 // box to thread w mod blockDim, in increasing w, so the counts and the summed
 // gains (binary64) are the same bits whatever the number of passes.
+//
+// Linear order: 4096 x 24 poses of 128x96 rays 55 ms with selects, 49 with
+// linear_step_idx.
 //
 // Eight waves per SIMD: the kernel fits 64 VGPRs, and left to itself the
 // compiler took 106 SGPRs, which allow only seven; with the hint it keeps 78
