@@ -134,15 +134,16 @@ __device__ __forceinline__ void word_coords(const DevMap& m, uint32_t idx, uint3
 // Bound by memory (4 B read, 4 B written per voxel).  Threads are dealt to the
 // padded grid's coordinates, so no index is divided (one thread per stored
 // word spent most of its time on four divisions per word: 50 us for 256^3 in
-// 4x4 columns, 33 now; 47 and 31 in linear order).
+// 4x4 columns, 33 now; 47 and 31 in linear order; with the codes 54 and 48,
+// 7 of them for the sampling pass).
 //
-// Every thread steps through LAYERS layers, their loads in flight together: 8,
-// or 1 for a map too small to fill the chip so (64^3 in columns: 6.2 us at 8,
+// Every thread steps through LAYERS layers, their loads in flight together: 4,
+// or 1 for a map too small to fill the chip so (64^3 in columns: 6.2 us at 8 layers,
 // 3.0 at 1).
 //
 // Linear order: a workgroup takes 64 words in x of 4 rows of y.
-constexpr int kEncodeLayers = 8;
-constexpr uint64_t kEncodeGroups = 2048;         // workgroups from which on they step through 8 layers
+constexpr int kEncodeLayers = 4;
+constexpr uint64_t kEncodeGroups = 2048;         // workgroups from which on they step through 4 layers
 
 template <int LAYERS>
 __global__ __launch_bounds__(256) void encode_linear_kernel(const float* __restrict__ prob,
@@ -199,7 +200,9 @@ __global__ __launch_bounds__(256) void encode_column_kernel(const float* __restr
     const int Z0 = ((int)blockIdx.z * 4 + wave) * LAYERS;
     __shared__ Palette s_pal;
     const bool coded = palette_load(s_pal, m);
-    if (tx >= m.nbx) return;
+    // (of a pair of 2x2 tiles one may lie beyond the grid: it helps to write the codes)
+    const bool stored = tx < m.nbx;
+    if (TL == 1 ? (tx & ~1) >= m.nbx : !stored) return;
     const int X = tx * T + (px % kCols) * 4, Y = ty * T + row;
     uint32_t* out = enc + ((size_t)(ty * m.nbx + tx) * m.pz << (2 * TL)) + row * T + (px % kCols) * 4;
     bool any_bad = false;
@@ -234,28 +237,46 @@ __global__ __launch_bounds__(256) void encode_column_kernel(const float* __restr
             int x, y;
             w[e] = at(e, x, y) && in_z ? encode_prob(p[k][e], occ_thr, free_thr, any_bad) : kSentinel;
         }
-        *reinterpret_cast<uint4*>(out + ((size_t)Z << (2 * TL))) = make_uint4(w[0], w[1], w[2], w[3]);
+        if (stored) *reinterpret_cast<uint4*>(out + ((size_t)Z << (2 * TL))) = make_uint4(w[0], w[1], w[2], w[3]);
         if (coded) {
+            if (w[0] == known && w[1] == known && w[2] == known && w[3] == known) {
+                codes[k] = code * 0x01010101u;   // most pieces of a map continue the one below
+            } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (w[e] != known) code = find_code(s_pal, m, known = w[e]);
-                codes[k] |= code << (8 * e);
+                for (int e = 0; e < 4; ++e) {
+                    if (w[e] != known) code = find_code(s_pal, m, known = w[e]);
+                    codes[k] |= code << (8 * e);
+                }
             }
         }
     }
     if (coded) {
         uint8_t* co = const_cast<uint8_t*>(m.codes);
         auto place = [&](int y, int Z) { return co + code_offset(m.csy, m.csz, (uint32_t)X, (uint32_t)y, (uint32_t)Z); };
-        if constexpr (TL == 1) {
-            // two codes of each of two rows
-#pragma unroll
-            for (int k = 0; k < LAYERS; ++k) {
-                if (Z0 + k >= m.pz) break;
-                *reinterpret_cast<uint16_t*>(place(Y, Z0 + k)) = (uint16_t)codes[k];
-                *reinterpret_cast<uint16_t*>(place(Y + 1, Z0 + k)) = (uint16_t)(codes[k] >> 16);
+        if constexpr (LAYERS == 1) {
+            if (Z0 < m.pz) {
+                if constexpr (TL == 1) {         // two codes of each of two rows
+                    *reinterpret_cast<uint16_t*>(place(Y, Z0)) = (uint16_t)codes[0];
+                    *reinterpret_cast<uint16_t*>(place(Y + 1, Z0)) = (uint16_t)(codes[0] >> 16);
+                } else {
+                    *reinterpret_cast<uint32_t*>(place(Y, Z0)) = codes[0];
+                }
             }
-        } else if constexpr (LAYERS == 1) {
-            if (Z0 < m.pz) *reinterpret_cast<uint32_t*>(place(Y, Z0)) = codes[0];
+        } else if constexpr (TL == 1) {
+            // two tiles of two layers are 16 consecutive codes: their lanes take every
+            // other pair of layers (see below)
+#pragma unroll
+            for (int k = 0; k < LAYERS; k += 2) {
+                const uint32_t o0 = (uint32_t)__shfl_xor((int)codes[k], 1, 64);
+                const uint32_t o1 = (uint32_t)__shfl_xor((int)codes[k + 1], 1, 64);
+                const int odd = tx & 1;
+                if (odd != (k / 2 & 1) || Z0 + k >= m.pz) continue;
+                const uint32_t a0 = odd ? o0 : codes[k], b0 = odd ? codes[k] : o0;
+                const uint32_t a1 = odd ? o1 : codes[k + 1], b1 = odd ? codes[k + 1] : o1;
+                *reinterpret_cast<uint4*>(place(Y, Z0 + k) - 2 * odd) =
+                    make_uint4((a0 & 0xFFFFu) | b0 << 16, a0 >> 16 | (b0 & 0xFFFF0000u), (a1 & 0xFFFFu) | b1 << 16,
+                               a1 >> 16 | (b1 & 0xFFFF0000u));
+            }
         } else {
             // two rows of two layers are 16 consecutive codes: the lanes of a pair of
             // rows exchange theirs and take every other pair of layers (the last
