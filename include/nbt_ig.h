@@ -135,7 +135,11 @@ int nbt_ig_ctx_get_map_layout(const nbt_ig_ctx* ctx, int* layout);
  * in [0,1]; HOST or DEVICE pointer) into a device-resident encoded map: each
  * voxel stores its Eq. 2 gain with the sign bit marking Occupied, inside a
  * one-voxel border that stops every ray leaving the map, stored in the
- * context's map layout.  1 <= n <= 4096 per axis and (nx+2)(ny+2)(nz+2) <
+ * context's map layout.  Beside words of more than 4 MiB the map holds a
+ * one-byte code per word and the palette of the words those codes stand for
+ * (a quarter of the words' memory again, not part of nbt_ig_map_info's
+ * device_bytes); a map with more different words than codes, or without
+ * memory for the codes, is walked by its words, with the same results.  1 <= n <= 4096 per axis and (nx+2)(ny+2)(nz+2) <
  * 2^30 (for the column orders: the count with x and y padded to whole tiles < 2^30).  `origin` (HOST, 3 floats) is the world
  * position of the min corner of voxel (0,0,0); `voxel_size` > 0 is s_Vox.
  * `cls` may be NULL (0.5/0.5); 0 <= free_threshold <= occ_threshold <= 1.
@@ -151,7 +155,8 @@ void nbt_ig_destroy_map(nbt_ig_map* map);        /* NULL is a no-op */
 /* Re-encodes an existing map in place from new probabilities of the same
  * dimensions (the map is rebuilt whenever a new point cloud has been fused,
  * Sec. III).  `prob` is a DEVICE pointer; the call is asynchronous on
- * `stream` and does not synchronise.  Values outside [0,1] or NaN are
+ * `stream` and does not synchronise (one launch, or two for a map with
+ * codes).  Values outside [0,1] or NaN are
  * encoded as Unknown and recorded; nbt_ig_map_check() synchronises `stream`
  * and returns NBT_IG_EINVAL if any update since the last check saw one.
  * Evaluations already enqueued on other streams must finish first. */
@@ -255,7 +260,12 @@ int nbt_ig_eval_viewpoints_noalloc(const nbt_ig_map* map, const nbt_ig_camera* c
  * Each trajectory's visited set is a bitset over the voxel box holding its
  * frusta, kept in LDS; a box with more bits than the context's LDS budget
  * holds is covered in several passes over the trajectory's rays, each marking
- * one slice of the box (same results, bit for bit).  Nothing is read back to
+ * one slice of the box (same results, bit for bit).  Few trajectories share
+ * the chip: several workgroups walk one trajectory and join their bitsets in
+ * device memory that the context allocates (128 MiB and a few slots) at the first such
+ * call that is not being captured; without it one workgroup walks each
+ * trajectory (the same counts; the union's sum is split otherwise, so its
+ * last place may differ).  Nothing is read back to
  * the host: the call only enqueues work on `stream` (so it can be captured in
  * a graph once a call with as many trajectories has sized the workspace).
  * n_traj == 0 is a no-op.
@@ -329,7 +339,9 @@ int nbt_ig_trace_paths(const nbt_ig_map* map, const nbt_ig_camera* cam, const fl
  * order (C <= 65536); pipeline_depth in
  * {1,2,4,8} map gathers in flight per ray (0 = default, 8).  A new context
  * starts at 4 waves, 8x8 tiles, balanced tiles per wave, no remap, 8 gathers
- * in flight.  Any shape gives the same step counts; IG agrees to the
+ * in flight.  While that starting shape stands, a call chooses for itself where another is
+ * faster: small calls walk each ray in segments on several lanes, calls of
+ * long rays run single-wave workgroups of one or two tiles.  Any shape gives the same step counts; IG agrees to the
  * last-place rounding of its sum.
  */
 typedef struct {

@@ -51,16 +51,11 @@ __device__ __forceinline__ void dda_advance_idx(float& tx, float& ty, float& tz,
     const bool bx = go && ex;
     const bool by = go && !ex && ey;
     const bool bz = go && !ex && !ey;
-    int d;
-    if constexpr (TL != 0) {
-        const uint32_t msk = bx ? tile_mask_x<TL>() : tile_mask_y<TL>();
-        const int big = bx ? bxo : byo;
-        const int small = bx ? dxo : dyo;
-        const int dxy = ((off ^ flip) & msk) == 0u ? big : small;
-        d = bz ? dzo : dxy;
-    } else {
-        d = bx ? dxo : (by ? dyo : dzo);
-    }
+    const uint32_t msk = bx ? tile_mask_x<TL>() : tile_mask_y<TL>();
+    const int big = bx ? bxo : byo;
+    const int small = bx ? dxo : dyo;
+    const int dxy = ((off ^ flip) & msk) == 0u ? big : small;
+    const int d = bz ? dzo : dxy;
     off = go ? off + (uint32_t)d : 0u;
     idx += bx ? dbx : (by ? dby : dbz);
     // the stepping axis gains its delta, the others add +0 (t >= 0, so exact):
