@@ -443,7 +443,7 @@ int nbt_ig_create_map(nbt_ig_ctx* ctx, const float* prob, int nx, int ny, int nz
     e = hipMemsetAsync(map->bad, 0, sizeof(unsigned int), s);
     if (e != hipSuccess) { rc = hip_fail(e, "hipMemsetAsync(flag)"); goto done; }
     e = launch_encode_map(src, map->enc, dm, c.occ_threshold, c.free_threshold, map->bad, s);
-    if (e != hipSuccess) { rc = hip_fail(e, "encode_map_kernel"); goto done; }
+    if (e != hipSuccess) { rc = hip_fail(e, "map encoding"); goto done; }
     e = hipMemcpyAsync(&bad, map->bad, sizeof bad, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) { rc = hip_fail(e, "map encode"); goto done; }
@@ -481,7 +481,7 @@ int nbt_ig_update_map(nbt_ig_map* map, const float* prob, void* stream) {
     if (!g.ok) return fail(NBT_IG_EDEVICE, "cannot select device %d", map->ctx->device);
     hipError_t e = launch_encode_map(prob, map->enc, map->dm, map->cls.occ_threshold,
                                      map->cls.free_threshold, map->bad, (hipStream_t)stream);
-    if (e != hipSuccess) return hip_fail(e, "encode_map_kernel");
+    if (e != hipSuccess) return hip_fail(e, "map encoding");
     return NBT_IG_OK;
 }
 
