@@ -36,41 +36,11 @@ __device__ __forceinline__ int32_t box_lin(const DevMap& m, int lx, int ly, int 
 }
 
 // dda_advance plus a second index (a bitset position) that moves with the
-// map offset: by dbx/dby/dbz per step on x/y/z.  Past the segment end it
-// drifts, but every slot from there on reads the sentinel and is never
-// marked, so it needs no gating.
-template <int TL>
-__device__ __forceinline__ void dda_advance_idx(float& tx, float& ty, float& tz, uint32_t& off,
-                                                int& idx, bool& alive, float t1, int dxo, int dyo, int dzo,
-                                                int bxo, int byo, uint32_t flip, int dbx, int dby,
-                                                int dbz, float dtx, float dty, float dtz) {
-    const float x = tx, y = ty, z = tz;
-    const float tm = fminf(fminf(x, y), z);
-    const bool go = alive && !(tm > t1);
-    const bool ex = x == tm, ey = y == tm;
-    const bool bx = go && ex;
-    const bool by = go && !ex && ey;
-    const bool bz = go && !ex && !ey;
-    const uint32_t msk = bx ? tile_mask_x<TL>() : tile_mask_y<TL>();
-    const int big = bx ? bxo : byo;
-    const int small = bx ? dxo : dyo;
-    const int dxy = ((off ^ flip) & msk) == 0u ? big : small;
-    const int d = bz ? dzo : dxy;
-    off = go ? off + (uint32_t)d : 0u;
-    idx += bx ? dbx : (by ? dby : dbz);
-    // the stepping axis gains its delta, the others add +0 (t >= 0, so exact):
-    // three selects and three adds instead of five selects and one add
-    tx = x + (bx ? dtx : 0.0f);
-    ty = y + (by ? dty : 0.0f);
-    tz = z + (bz ? dtz : 0.0f);
-    alive = go;
-}
-
-// dda_advance_idx for the linear order, for the lanes that execute it.  The
-// three-way choice is made with the execution mask, as in code_step: the
-// lanes of one axis add its dt, map stride and bitset stride, then the next
-// axis' do; lanes past their segment's end t1 are sent to the corner
-// sentinel and stay there.  14 VALU operations, four of them compares, where
+// map offset, by dbx/dby/dbz per step on x/y/z; linear order, for the lanes
+// that execute it.  The three-way choice is made with the execution mask, as
+// in code_step: the lanes of one axis add its dt, map stride and bitset
+// stride, then the next axis' do; lanes past their segment's end t1 are sent
+// to the corner sentinel and stay there.  14 VALU operations, four of them compares, where
 // the selects made 15 of which ten issue at half rate.  `past`: those lanes.
 __device__ __forceinline__ void linear_step_idx(float& tx, float& ty, float& tz, uint32_t& off, int& idx,
                                                 uint64_t& past, float t1, int dxo, int dyo, int dzo, int dbx, int dby,
@@ -107,19 +77,65 @@ __device__ __forceinline__ void linear_step_idx(float& tx, float& ty, float& tz,
         : "scc");
 }
 
+// The same in column order: an x or y step adds the big stride where it
+// leaves the tile, which its lanes alone test.  20 VALU operations, seven of
+// them compares or selects, where selects all through made 24 with 15 of them:
+// 4096 x 24 poses of 128x96 rays 63.7 ms with selects, 59.0 so (any tile size).
+template <int TL>
+__device__ __forceinline__ void column_step_idx(float& tx, float& ty, float& tz, uint32_t& off, int& idx,
+                                                uint64_t& past, float t1, const OffsetSteps& o, int dbx, int dby,
+                                                int dbz, float dtx, float dty, float dtz) {
+    float t;
+    uint32_t d;
+    uint64_t all, a, b, big;
+    asm("v_min3_f32 %[t], %[tx], %[ty], %[tz]\n\t"
+        "s_mov_b64 %[all], exec\n\t"
+        "v_cmp_gt_f32_e64 %[past], %[t], %[t1]\n\t"
+        "s_and_b64 exec, %[all], %[past]\n\t"
+        "v_mov_b32_e32 %[off], 0\n\t"
+        "s_andn2_b64 exec, %[all], %[past]\n\t"
+        "s_mov_b64 %[b], exec\n\t"
+        "v_cmpx_eq_f32_e64 %[a], %[tx], %[t]\n\t"          // the lanes that step on x
+        "v_bitop3_b32 %[d], %[off], %[flip], %[mx] bitop3:0x28\n\t"      // (off ^ flip) & mask
+        "v_cmp_eq_u32_e64 %[big], 0, %[d]\n\t"
+        "v_add_f32_e32 %[tx], %[tx], %[dtx]\n\t"           // two instructions before `big` may be read
+        "v_add_u32_e32 %[idx], %[idx], %[dbx]\n\t"
+        "v_cndmask_b32_e64 %[d], %[dxo], %[bxo], %[big]\n\t"
+        "v_add_u32_e32 %[off], %[off], %[d]\n\t"
+        "s_andn2_b64 exec, %[b], %[a]\n\t"
+        "s_andn2_b64 %[b], %[b], %[a]\n\t"
+        "v_cmpx_eq_f32_e64 %[a], %[ty], %[t]\n\t"          // of the others, those on y
+        "v_bitop3_b32 %[d], %[off], %[flip], %[my] bitop3:0x28\n\t"
+        "v_cmp_eq_u32_e64 %[big], 0, %[d]\n\t"
+        "v_add_f32_e32 %[ty], %[ty], %[dty]\n\t"
+        "v_add_u32_e32 %[idx], %[idx], %[dby]\n\t"
+        "v_cndmask_b32_e64 %[d], %[dyo], %[byo], %[big]\n\t"
+        "v_add_u32_e32 %[off], %[off], %[d]\n\t"
+        "s_andn2_b64 exec, %[b], %[a]\n\t"                 // the rest on z
+        "v_add_f32_e32 %[tz], %[tz], %[dtz]\n\t"
+        "v_add_u32_e32 %[off], %[off], %[dzo]\n\t"
+        "v_add_u32_e32 %[idx], %[idx], %[dbz]\n\t"
+        "s_mov_b64 exec, %[all]\n\t"
+        "s_nop 1"                                            // past may be read as a VALU operand next
+        : [tx] "+v"(tx), [ty] "+v"(ty), [tz] "+v"(tz), [off] "+v"(off), [idx] "+v"(idx), [t] "=&v"(t),
+          [d] "=&v"(d), [all] "=&s"(all), [a] "=&s"(a), [b] "=&s"(b), [past] "=&s"(past), [big] "=&s"(big)
+        : [t1] "v"(t1), [dxo] "v"(o.dx), [bxo] "v"(o.bigx), [dyo] "v"(o.dy), [byo] "v"(o.bigy), [dzo] "v"(o.dz),
+          [flip] "v"(o.flip), [mx] "s"(tile_mask_x<TL>()), [my] "s"(tile_mask_y<TL>()), [dbx] "v"(dbx),
+          [dby] "v"(dby), [dbz] "v"(dbz), [dtx] "v"(dtx), [dty] "v"(dty), [dtz] "v"(dtz)
+        : "scc");
+}
+
 // One generator step of the union walk.  alive: still inside the segment.
 template <int TL, bool ALIVE>
 __device__ __forceinline__ void union_advance(float& tx, float& ty, float& tz, uint32_t& off, int& idx, bool& alive,
                                               float t1, const OffsetSteps& o, int dbx, int dby, int dbz, float dtx,
                                               float dty, float dtz) {
-    if constexpr (TL == 0) {
-        uint64_t past;
+    uint64_t past;
+    if constexpr (TL == 0)
         linear_step_idx(tx, ty, tz, off, idx, past, t1, o.dx, o.dy, o.dz, dbx, dby, dbz, dtx, dty, dtz);
-        if constexpr (ALIVE) alive = !__builtin_amdgcn_inverse_ballot_w64(past);
-    } else {
-        dda_advance_idx<TL>(tx, ty, tz, off, idx, alive, t1, o.dx, o.dy, o.dz, o.bigx, o.bigy, o.flip, dbx, dby, dbz,
-                            dtx, dty, dtz);
-    }
+    else
+        column_step_idx<TL>(tx, ty, tz, off, idx, past, t1, o, dbx, dby, dbz, dtx, dty, dtz);
+    if constexpr (ALIVE) alive = !__builtin_amdgcn_inverse_ballot_w64(past);
 }
 
 // Pipelined walk that also sets, in the LDS bitset `bits`, the bit of every
@@ -327,8 +343,8 @@ __global__ __launch_bounds__(256) void traj_box_kernel(DevMap m, CamParams c,
 // box to thread w mod blockDim, in increasing w, so the counts and the summed
 // gains (binary64) are the same bits whatever the number of passes.
 //
-// Linear order: 4096 x 24 poses of 128x96 rays 55 ms with selects, 49 with
-// linear_step_idx.
+// 4096 x 24 poses of 128x96 rays: linear order 55 ms with selects, 48-49 with
+// linear_step_idx; column orders 63.7 and, with column_step_idx, 59.
 //
 // Eight waves per SIMD: the kernel fits 64 VGPRs, and left to itself the
 // compiler took 106 SGPRs, which allow only seven; with the hint it keeps 78
