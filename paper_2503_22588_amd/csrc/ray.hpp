@@ -334,39 +334,87 @@ __device__ __forceinline__ OffsetSteps offset_steps(const DevMap& m, const RaySt
 // generator points at offset 0, the sentinel word in the corner of the
 // border (either layout), so every later gather reads "stop" without the
 // loaded value ever being inspected here (which would force a wait for it).
-// Loop invariants are passed by value so that the axis choice stays a
-// register select.
+//
+// The three-way choice is made with the execution mask, as in code_step, and
+// the lanes of x and of y alone test their tile's face: 17 VALU operations in
+// column order, six of them compares or selects, where selects all through took 20,
+// 13 of which issue at half rate.  A lane past the end keeps its t and
+// so stays past it.  32 perspectives of 64x48 rays in a 64^3 map 16.0 -> 14.9 us,
+// a batch of 64 maps 2.54 -> 2.50 ms, whose larger maps are walked by codes.
 template <int TL>
 __device__ __forceinline__ void dda_advance(float& tx, float& ty, float& tz, uint32_t& off,
                                             bool& alive, float t1, int dxo, int dyo, int dzo,
                                             int bxo, int byo, uint32_t flip,
                                             float dtx, float dty, float dtz) {
-    const float x = tx, y = ty, z = tz;
-    const float tm = fminf(fminf(x, y), z);
-    const bool go = alive && !(tm > t1);
-    const bool ex = x == tm, ey = y == tm;
-    const bool bx = go && ex;
-    const bool by = go && !ex && ey;
-    const bool bz = go && !ex && !ey;
-    int d;
-    if constexpr (TL != 0) {
-        // x or y: the in-tile stride, or the tile-crossing delta at the tile
-        // face; z: one layer.  Two selects fewer than a 3-axis edge test.
-        const uint32_t msk = bx ? tile_mask_x<TL>() : tile_mask_y<TL>();
-        const int big = bx ? bxo : byo;
-        const int small = bx ? dxo : dyo;
-        const int dxy = ((off ^ flip) & msk) == 0u ? big : small;
-        d = bz ? dzo : dxy;
+    float t;
+    uint64_t all, a, b, past;
+    if constexpr (TL == 0) {
+        asm("v_min3_f32 %[t], %[tx], %[ty], %[tz]\n\t"
+            "s_mov_b64 %[all], exec\n\t"
+            "v_cmp_gt_f32_e64 %[past], %[t], %[t1]\n\t"
+            "s_and_b64 exec, %[all], %[past]\n\t"
+            "v_mov_b32_e32 %[off], 0\n\t"
+            "s_andn2_b64 exec, %[all], %[past]\n\t"
+            "s_mov_b64 %[b], exec\n\t"
+            "v_cmpx_eq_f32_e64 %[a], %[tx], %[t]\n\t"          // the lanes that step on x
+            "v_add_f32_e32 %[tx], %[tx], %[dtx]\n\t"
+            "v_add_u32_e32 %[off], %[off], %[dxo]\n\t"
+            "s_andn2_b64 exec, %[b], %[a]\n\t"
+            "s_andn2_b64 %[b], %[b], %[a]\n\t"
+            "v_cmpx_eq_f32_e64 %[a], %[ty], %[t]\n\t"          // of the others, those on y
+            "v_add_f32_e32 %[ty], %[ty], %[dty]\n\t"
+            "v_add_u32_e32 %[off], %[off], %[dyo]\n\t"
+            "s_andn2_b64 exec, %[b], %[a]\n\t"                 // the rest on z
+            "v_add_f32_e32 %[tz], %[tz], %[dtz]\n\t"
+            "v_add_u32_e32 %[off], %[off], %[dzo]\n\t"
+            "s_mov_b64 exec, %[all]\n\t"
+            "s_nop 1"                                            // past may be read as a VALU operand next
+            : [tx] "+v"(tx), [ty] "+v"(ty), [tz] "+v"(tz), [off] "+v"(off), [t] "=&v"(t), [all] "=&s"(all),
+              [a] "=&s"(a), [b] "=&s"(b), [past] "=&s"(past)
+            : [t1] "v"(t1), [dxo] "v"(dxo), [dyo] "v"(dyo), [dzo] "v"(dzo), [dtx] "v"(dtx), [dty] "v"(dty),
+              [dtz] "v"(dtz)
+            : "scc");
     } else {
-        d = bx ? dxo : (by ? dyo : dzo);
+        // x or y: the in-tile stride, or the tile-crossing delta at the tile
+        // face; z: one layer.
+        uint32_t d;
+        uint64_t big;
+        asm("v_min3_f32 %[t], %[tx], %[ty], %[tz]\n\t"
+            "s_mov_b64 %[all], exec\n\t"
+            "v_cmp_gt_f32_e64 %[past], %[t], %[t1]\n\t"
+            "s_and_b64 exec, %[all], %[past]\n\t"
+            "v_mov_b32_e32 %[off], 0\n\t"
+            "s_andn2_b64 exec, %[all], %[past]\n\t"
+            "s_mov_b64 %[b], exec\n\t"
+            "v_cmpx_eq_f32_e64 %[a], %[tx], %[t]\n\t"
+            "v_bitop3_b32 %[d], %[off], %[flip], %[mx] bitop3:0x28\n\t"      // (off ^ flip) & mask
+            "v_cmp_eq_u32_e64 %[big], 0, %[d]\n\t"
+            "v_add_f32_e32 %[tx], %[tx], %[dtx]\n\t"
+            "s_nop 0\n\t"                                      // two states before `big` may be read
+            "v_cndmask_b32_e64 %[d], %[dxo], %[bxo], %[big]\n\t"
+            "v_add_u32_e32 %[off], %[off], %[d]\n\t"
+            "s_andn2_b64 exec, %[b], %[a]\n\t"
+            "s_andn2_b64 %[b], %[b], %[a]\n\t"
+            "v_cmpx_eq_f32_e64 %[a], %[ty], %[t]\n\t"
+            "v_bitop3_b32 %[d], %[off], %[flip], %[my] bitop3:0x28\n\t"
+            "v_cmp_eq_u32_e64 %[big], 0, %[d]\n\t"
+            "v_add_f32_e32 %[ty], %[ty], %[dty]\n\t"
+            "s_nop 0\n\t"
+            "v_cndmask_b32_e64 %[d], %[dyo], %[byo], %[big]\n\t"
+            "v_add_u32_e32 %[off], %[off], %[d]\n\t"
+            "s_andn2_b64 exec, %[b], %[a]\n\t"
+            "v_add_f32_e32 %[tz], %[tz], %[dtz]\n\t"
+            "v_add_u32_e32 %[off], %[off], %[dzo]\n\t"
+            "s_mov_b64 exec, %[all]\n\t"
+            "s_nop 1"
+            : [tx] "+v"(tx), [ty] "+v"(ty), [tz] "+v"(tz), [off] "+v"(off), [t] "=&v"(t), [d] "=&v"(d),
+              [all] "=&s"(all), [a] "=&s"(a), [b] "=&s"(b), [past] "=&s"(past), [big] "=&s"(big)
+            : [t1] "v"(t1), [dxo] "v"(dxo), [bxo] "v"(bxo), [dyo] "v"(dyo), [byo] "v"(byo), [dzo] "v"(dzo),
+              [flip] "v"(flip), [mx] "s"(tile_mask_x<TL>()), [my] "s"(tile_mask_y<TL>()), [dtx] "v"(dtx),
+              [dty] "v"(dty), [dtz] "v"(dtz)
+            : "scc");
     }
-    off = go ? off + (uint32_t)d : 0u;
-    // the stepping axis gains its delta, the others add +0 (t >= 0, so exact):
-    // three selects and three adds instead of five selects and one add
-    tx = x + (bx ? dtx : 0.0f);
-    ty = y + (by ? dty : 0.0f);
-    tz = z + (bz ? dtz : 0.0f);
-    alive = go;
+    alive = !__builtin_amdgcn_inverse_ballot_w64(past);
 }
 
 // Software-pipelined walk for the throughput kernels.  The voxel sequence of
@@ -477,7 +525,7 @@ __device__ __forceinline__ void walk_ray_pipelined(const DevMap& m, __amdgpu_buf
 // moves, so the three-way choice is made with the execution mask instead: the
 // lanes of one axis add their dt and fetch the axis' mask, then the next
 // axis' do.  The mask is what it was at the end.  17 VALU operations per
-// voxel with the sum and the palette, 24 in the word walk.
+// voxel with the sum and the palette; selects took 24 by words.
 __device__ __forceinline__ void code_step(float& tx, float& ty, float& tz, uint32_t& g, uint64_t& past, float t1,
                                           uint32_t mx, uint32_t my, uint32_t mz, float dtx, float dty, float dtz) {
     uint32_t mask, t;
