@@ -24,13 +24,13 @@ struct RayState {
     float t1;                // end of the clipped segment
 };
 
-__device__ __forceinline__ float sel_min(float a, float b) { return (b < a) ? b : a; }
-__device__ __forceinline__ float sel_max(float a, float b) { return (b > a) ? b : a; }
+__host__ __device__ __forceinline__ float sel_min(float a, float b) { return (b < a) ? b : a; }
+__host__ __device__ __forceinline__ float sel_max(float a, float b) { return (b > a) ? b : a; }
 
 // One axis of the slab clip.  Returns false when the ray runs parallel to
 // this axis' faces outside the map.
-__device__ __forceinline__ bool clip_axis(float O, float D, int n, float& t0, float& t1,
-                                          float& inv, bool& parallel) {
+__host__ __device__ __forceinline__ bool clip_axis(float O, float D, int n, float& t0, float& t1,
+                                                   float& inv, bool& parallel) {
     parallel = fabsf(D) < 0x1p-100f;
     if (parallel) {
         inv = 0.0f;
@@ -44,8 +44,8 @@ __device__ __forceinline__ bool clip_axis(float O, float D, int n, float& t0, fl
     return true;
 }
 
-__device__ __forceinline__ void init_axis(float O, float D, float t0, float inv, bool parallel,
-                                          int n, int& idx, int& step, float& tmax, float& tdelta) {
+__host__ __device__ __forceinline__ void init_axis(float O, float D, float t0, float inv, bool parallel,
+                                                   int n, int& idx, int& step, float& tmax, float& tdelta) {
     float f = floorf(O + t0 * D);
     f = sel_max(f, 0.0f);
     f = sel_min(f, (float)(n - 1));
