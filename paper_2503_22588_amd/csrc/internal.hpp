@@ -106,12 +106,21 @@ struct CamParams {
 // bit-identical whatever order the workgroups finish in.  The last
 // workgroup of a perspective reads and clears its slot.
 struct VpAccum {
-    unsigned long long sum_fx;     // sum of ray gains * 2^24, rounded per workgroup
+    unsigned long long sum_fx;     // sum of ray gains * fix_scale, rounded per workgroup
     unsigned long long steps;
     unsigned int count;            // workgroups done
     unsigned int invalid;
 };
-constexpr double kFixScale = 16777216.0;     // 2^24
+// The scale of those sums: the power of two that keeps the most a perspective
+// can gather (1 a visit, nx + ny + nz + 3 visits a ray) below 2^63.  2^39 for
+// 64x48 rays in a 1024^3 map, 2^27 at the largest sizes accepted, so rounding
+// a workgroup's sum costs no more than 2^-28 of one Unknown voxel's gain (a
+// fixed 2^24 lost whole digits of perspectives that see small gains only).
+__host__ __device__ inline double fix_scale(const DevMap& m, const CamParams& c) {
+    const unsigned long long most = (unsigned long long)c.W * (unsigned long long)c.H *
+                                    (unsigned long long)(m.nx + m.ny + m.nz + 3);
+    return (double)(1ull << (__builtin_clzll(most) - 1));
+}
 
 // Launch shape of the viewpoint kernel.
 struct VpLaunch {

@@ -39,7 +39,7 @@ __device__ __forceinline__ uint32_t xcd_logical(uint32_t bid, uint32_t nb, uint3
 // the whole block.
 template <int WAVES>
 __device__ __forceinline__ void vp_combine(int waves, double acc, uint32_t steps, bool invalid, uint32_t vp,
-                                           uint32_t groups, double rays, float* __restrict__ ig_out,
+                                           uint32_t groups, double rays, double scale, float* __restrict__ ig_out,
                                            unsigned long long* __restrict__ steps_out,
                                            VpAccum* __restrict__ ws) {
     const int wave = threadIdx.x >> 6;
@@ -88,7 +88,7 @@ __device__ __forceinline__ void vp_combine(int waves, double acc, uint32_t steps
     // invalidates it (the map's gathers of the other workgroups there then
     // miss); they cost 8-15 % of a call of 64-256 perspectives of 64x48 rays.
     VpAccum* a = ws + vp;
-    const unsigned long long o_sum = atomicAdd(&a->sum_fx, __double2ull_rn(tot * kFixScale));
+    const unsigned long long o_sum = atomicAdd(&a->sum_fx, __double2ull_rn(tot * scale));
     const unsigned long long o_steps = atomicAdd(&a->steps, st);
     const unsigned int o_inv = inv ? atomicOr(&a->invalid, 1u) : 0u;
     unsigned int one = 1u;
@@ -99,7 +99,7 @@ __device__ __forceinline__ void vp_combine(int waves, double acc, uint32_t steps
         const unsigned long long stp = atomicExch(&a->steps, 0ull);
         const unsigned int iv = atomicExch(&a->invalid, 0u);
         atomicExch(&a->count, 0u);
-        ig_out[vp] = iv ? __builtin_nanf("") : (float)(((double)s / kFixScale) / rays);
+        ig_out[vp] = iv ? __builtin_nanf("") : (float)(((double)s / scale) / rays);
         if (steps_out) steps_out[vp] = stp;
     }
 }
@@ -198,7 +198,8 @@ __device__ __forceinline__ void vp_group(const DevMap& m, const CamParams& c,
         }
     }
 
-    vp_combine<WAVES>(WAVES, acc, steps, invalid, vp, groups, (double)c.W * (double)c.H, ig_out, steps_out, ws);
+    vp_combine<WAVES>(WAVES, acc, steps, invalid, vp, groups, (double)c.W * (double)c.H, fix_scale(m, c), ig_out,
+                      steps_out, ws);
 }
 
 // CODED: the map has codes (walked by them unless its palette overflowed).
@@ -400,7 +401,7 @@ __global__ __launch_bounds__(kSegThreads) void ig_segments_kernel(DevMap m, CamP
         steps = 0u;
     }
     vp_combine<kSegThreads / 64>((int)(blockDim.x >> 6), acc, steps, seg == 0u && st == kRayInvalid, vp, L.groups,
-                  (double)c.W * (double)c.H, ig_out, steps_out, ws);
+                                  (double)c.W * (double)c.H, fix_scale(m, c), ig_out, steps_out, ws);
 }
 
 // Persistent batched launch: many maps, a CSR of perspectives per map
