@@ -157,7 +157,6 @@ struct TrajBox {
 // slot, both cleared by the box pre-pass of every call.
 constexpr uint32_t kTrajSplitMost = 2048;            // trajectories of a split call
 constexpr uint32_t kTrajSplitWords = 32u << 20;      // bitset words of all of them (128 MiB)
-constexpr uint32_t kTrajSplitCap = 1u << 16;         // bitset words of one of them at most
 constexpr int kTrajParts = 64;                       // workgroups that sum up one trajectory at most
 struct TrajAccum {
     unsigned long long visits;
@@ -169,6 +168,7 @@ struct TrajAccum {
 
 // How a call of T trajectories is split; groups == 1: one workgroup each.
 struct TrajSplit {
+    uint32_t trajectories;
     uint32_t groups;         // workgroups that share one trajectory's rays
     uint32_t parts;          // workgroups that sum up its bitset
     uint32_t cap_words;      // bitset words per trajectory; a larger box is left to one workgroup

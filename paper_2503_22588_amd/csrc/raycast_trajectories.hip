@@ -355,7 +355,12 @@ __global__ __launch_bounds__(256) void traj_box_kernel(DevMap m, CamParams c,
 // contiguous run of the tile order (a few pixel tiles, all poses: the voxels
 // of different workgroups overlap little) into a bitset of its own and ORs
 // its nonzero words into the trajectory's bitset in memory; traj_sum_kernel
-// sums that up.  A box larger than the scratch is left to one workgroup.
+// sums that up.  A box larger than a trajectory's share of the scratch is left
+// to one workgroup: one for each trajectory leads the grid, so that these long
+// ones start first and one to a CU (among the workgroups of a trajectory they
+// were groups apart, a multiple of 8 as often as not: on one XCD of eight.
+// 200 x 12 poses of 64x48 rays at 2 cm, most boxes larger: 24 ms unsplit, 77 so.
+// 300 x 4 poses at 1 cm: 60 ms unsplit, 109 so, 60 with the leading workgroups).
 template <int WAVES, bool COUNT, bool TRACE, bool SPLIT>
 __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(8, 8))) void traj_union_kernel(
     DevMap m, CamParams c, const float* __restrict__ poses, uint32_t L,
@@ -363,11 +368,13 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(8, 8
     uint32_t* __restrict__ counts, unsigned long long* __restrict__ visits,
     nbt_ig_ray_digest* __restrict__ trace, TrajSplit split) {
     extern __shared__ uint32_t lds_bits[];
-    const uint32_t t = SPLIT ? blockIdx.x / split.groups : blockIdx.x;
+    const bool front = !SPLIT || blockIdx.x < split.trajectories;
+    const uint32_t slot = front ? blockIdx.x : blockIdx.x - split.trajectories;
+    const uint32_t t = front ? slot : slot / split.groups;
     const TrajBox b = boxes[t];
     const bool whole = !SPLIT || ((uint64_t)b.nbits + 31u) / 32u > split.cap_words;
-    const uint32_t part = SPLIT ? blockIdx.x - t * split.groups : 0u;
-    if (SPLIT && whole && part != 0u) return;
+    if (whole != front) return;
+    const uint32_t part = front ? 0u : slot - t * split.groups;
     // the bitset follows the walk's all-ones word and holds the clamp bit
     uint32_t* bits = lds_bits + 1;
     const uint32_t tid = threadIdx.x;
@@ -649,7 +656,7 @@ static hipError_t launch_union(const DevMap& m, const CamParams& c, const float*
     static std::atomic<size_t> lds_set[64];
     hipError_t e = allow_dynamic_lds(k, lds, lds_set, 64);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((traj_union_kernel<WAVES, COUNT, TRACE, SPLIT>), dim3(SPLIT ? T * split.groups : T),
+    hipLaunchKernelGGL((traj_union_kernel<WAVES, COUNT, TRACE, SPLIT>), dim3(SPLIT ? T * (split.groups + 1u) : T),
                        dim3(WAVES * 64), lds, s, m, c, poses, L, boxes, pass_words, ig_union, counts, visits, trace,
                        split);
     e = hipGetLastError();
