@@ -7,18 +7,20 @@
 //         PoI, 0 when the PoI is outside the field of view;
 //   c_I   sum over a horizon's states of w_I / (O G + eps).
 // ALU-bound: about 10 VALU operations (one of them a quarter-rate reciprocal)
-// per (state, perspective) pair.  One lane per state and 16 waves per
+// per (state, perspective) pair.  One lane per state and up to 16 waves per
 // workgroup that split the perspectives: a planner's call
 // has few states (256 horizons of 20 states are 86 workgroups), so the
 // parallelism has to come from the perspectives.  A perspective's position
 // and IG are the same for the whole wave and are read through scalar loads.
-// The waves split the perspectives of 16 distributions at a time as one row,
+// The waves split the perspectives of as many distributions at a time as one row,
 // so there are two barriers for 16 of them (split one by one, the workgroup
 // waited 2.4 us per distribution for the wave that summed up the last).
 // 256 x 20 states against 10 x 500 perspectives: 671 us with one thread per
 // state over all perspectives (20 workgroups of 4 waves on the chip) and 5 us
 // for the horizons' sum in a launch of its own; 29 us in this kernel, 17 in
-// the one below.  1024 horizons: 55 us here, 58 there; 4096: 160 and 215.
+// the one below.  1024 horizons: 55 us here, 58 there; 4096: 131 and 203.
+#include <algorithm>
+
 #include "internal.hpp"
 
 namespace nbt {
@@ -99,15 +101,15 @@ __device__ __forceinline__ void idw_pair(IdwSums& a, float dx, float dy, float d
 // split evenly, so a wave's stretch touches at most two of them;
 // add(sums, u, j0, j1) adds its share of perspectives j0..j1 - 1 of distribution u.  The
 // total is in wave 0.
-template <class Add>
+template <int WAVES, class Add>
 __device__ __forceinline__ double idw_sum(uint32_t nb, uint32_t np, int lane, uint32_t wave, uint32_t states,
                                           uint32_t subs, Add&& add) {
-    __shared__ double s_num[2][kCostWaves][64], s_den[2][kCostWaves][64], s_num0[2][kCostWaves][64];
-    __shared__ uint32_t s_cnt0[2][kCostWaves][64];
+    __shared__ double s_num[2][WAVES][64], s_den[2][WAVES][64], s_num0[2][WAVES][64];
+    __shared__ uint32_t s_cnt0[2][WAVES][64];
     double g_sum = 0.0;                          // of the distributions this wave sums up
-    for (uint32_t u0 = 0; u0 < nb; u0 += kCostWaves) {
-        const uint32_t count = min(nb - u0, (uint32_t)kCostWaves), row = count * np;
-        const uint32_t share = (row + kCostWaves - 1) / kCostWaves;
+    for (uint32_t u0 = 0; u0 < nb; u0 += WAVES) {
+        const uint32_t count = min(nb - u0, (uint32_t)WAVES), row = count * np;
+        const uint32_t share = (row + WAVES - 1) / WAVES;
         uint32_t i = min(wave * share, row);
         const uint32_t end = min(i + share, row);
         for (uint32_t e = 0; i < end; ++e) {
@@ -157,13 +159,13 @@ __device__ __forceinline__ double idw_sum(uint32_t nb, uint32_t np, int lane, ui
     g_sum = 0.0;
     if (wave == 0u) {
 #pragma unroll
-        for (int w = 0; w < kCostWaves; ++w) g_sum += s_num[0][w][lane];
+        for (int w = 0; w < WAVES; ++w) g_sum += s_num[0][w][lane];
     }
     return g_sum;
 }
 
-template <bool P_TWO>
-__global__ __launch_bounds__(kCostWaves * 64) void idw_query_kernel(
+template <bool P_TWO, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void idw_query_kernel(
     const float* __restrict__ id_pos, const float* __restrict__ id_ig, uint32_t nb, uint32_t np, float p,
     const float* __restrict__ poses, uint32_t q_count, uint32_t tile, uint32_t steps, float px, float py,
     float pz, float tan_h, float tan_v, float w_i, float eps, float* __restrict__ g_out,
@@ -180,7 +182,7 @@ __global__ __launch_bounds__(kCostWaves * 64) void idw_query_kernel(
         tz = poses[12 * (size_t)q + 11];
     }
     const float half_neg_p = -0.5f * p;
-    const double g = idw_sum(nb, np, lane, wave, 64u, 1u, [&](IdwSums& a, uint32_t u, uint32_t j0, uint32_t j1) {
+    const double g = idw_sum<WAVES>(nb, np, lane, wave, 64u, 1u, [&](IdwSums& a, uint32_t u, uint32_t j0, uint32_t j1) {
         for (uint32_t r = j0; r < j1; r += kCostRun) {
             const uint32_t end = min(r + (uint32_t)kCostRun, j1);
             uint32_t j = r;
@@ -249,7 +251,7 @@ __global__ __launch_bounds__(kCostWaves * 64) void idw_horizon_kernel(
         tz = poses[12 * (size_t)q + 11];
     }
     const float half_neg_p = -0.5f * p;
-    const double g = idw_sum(nb, np, lane, wave, steps, subs, [&](IdwSums& a, uint32_t u, uint32_t j0, uint32_t j1) {
+    const double g = idw_sum<kCostWaves>(nb, np, lane, wave, steps, subs, [&](IdwSums& a, uint32_t u, uint32_t j0, uint32_t j1) {
         float4 next = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         auto fetch = [&](uint32_t j) {
             if (j < j1) {
@@ -315,19 +317,43 @@ __global__ __launch_bounds__(256) void horizon_cost_kernel(const float* __restri
     cost[i] = (float)s;
 }
 
+// One horizon per workgroup pays while all of them run at once and each has
+// enough perspectives to split: 256 x 20 states against 10 x 500 17 us where
+// tiles take 29, 300 x 20 28 and 28 (32 and 35 for p = 1), 512 x 20 31 and 30, 16 x 1 18 and 27; with 1 x 500 or fewer, or distributions of
+// 16 perspectives, which leave most lanes of a wave's chunk of 64 idle, it takes
+// longer (256 x 1: 9.7 and 7.2; 64 x 16 perspectives 82 and 11).
+static bool horizon_alone(uint32_t h, uint32_t k, uint32_t nb, uint32_t np, int cu_count) {
+    return k <= 32 && 2u * h <= 3u * (uint32_t)cu_count && np >= 128 && (uint64_t)nb * np >= 1000;
+}
+
+// Waves that split a tile's perspectives: 10 perspectives each at least, and
+// no more than the chip holds at once (24 a CU), since every workgroup pays
+// for its barriers and the sums' way through LDS.  16 waves for all: 1e6 x 1
+// states against 1 x 10 128 us, one wave 16; 30,000 x 20 against 1 x 100 150, two 30; 10,000 x 100
+// against 10 x 500 1557, two 1138.  In a large call one wave alone is slower
+// with many perspectives (1223 there), two are within 5 % of the best.
+static int query_waves(uint32_t tiles, uint32_t nb, uint32_t np, int cu_count) {
+    const uint64_t pairs = (uint64_t)nb * np, cu = (uint64_t)cu_count;
+    const uint64_t least = tiles >= 32u * cu ? 2u : 4u;
+    const uint64_t most = std::min(pairs / 10u, std::max(24u * cu / tiles, least));
+    int w = kCostWaves;
+    while (w > 1 && (uint64_t)w > most) w /= 2;
+    return w;
+}
+
 hipError_t launch_eval_cost(const float* id_pos, const float* id_ig, uint32_t nb, uint32_t np, float p,
                             const float* poses, uint32_t h, uint32_t k, const float poi[3], float tan_h,
                             float tan_v, float w_i, float eps, float* g_out, float* o_out, float* cost,
                             int cu_count, hipStream_t s) {
     const uint32_t q = h * k;
     const uint32_t tile = cost_tile(k);
-    auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((q + tile - 1) / tile), dim3(kCostWaves * 64), 0, s, id_pos, id_ig, nb, np,
+    const uint32_t tiles = (q + tile - 1) / tile;
+    auto go = [&](auto kernel, int waves) {
+        hipLaunchKernelGGL(kernel, dim3(tiles), dim3(waves * 64), 0, s, id_pos, id_ig, nb, np,
                            p, poses, q, tile, k, poi[0], poi[1], poi[2], tan_h, tan_v, w_i, eps, g_out, o_out,
                            k <= 64 ? cost : nullptr);
     };
-    // one horizon a workgroup where whole tiles would leave compute units idle
-    if (k <= 32 && (q + tile - 1) / tile < (uint32_t)cu_count) {
+    if (horizon_alone(h, k, nb, np, cu_count)) {
         auto one = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3(h), dim3(kCostWaves * 64), 0, s, id_pos, id_ig, nb, np, p, poses, q, k,
                                64 / k, poi[0], poi[1], poi[2], tan_h, tan_v, w_i, eps, g_out, o_out, cost);
@@ -336,8 +362,14 @@ hipError_t launch_eval_cost(const float* id_pos, const float* id_ig, uint32_t nb
         else one(idw_horizon_kernel<false>);
         return hipGetLastError();
     }
-    if (p == 2.0f) go(idw_query_kernel<true>);
-    else go(idw_query_kernel<false>);
+    const bool two = p == 2.0f;
+    switch (query_waves(tiles, nb, np, cu_count)) {
+    case 1: two ? go(idw_query_kernel<true, 1>, 1) : go(idw_query_kernel<false, 1>, 1); break;
+    case 2: two ? go(idw_query_kernel<true, 2>, 2) : go(idw_query_kernel<false, 2>, 2); break;
+    case 4: two ? go(idw_query_kernel<true, 4>, 4) : go(idw_query_kernel<false, 4>, 4); break;
+    case 8: two ? go(idw_query_kernel<true, 8>, 8) : go(idw_query_kernel<false, 8>, 8); break;
+    default: two ? go(idw_query_kernel<true, 16>, 16) : go(idw_query_kernel<false, 16>, 16);
+    }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || !cost || k <= 64) return e;
     hipLaunchKernelGGL(horizon_cost_kernel, dim3((h + 255) / 256), dim3(256), 0, s, g_out, o_out, h, k, w_i,
