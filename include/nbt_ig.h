@@ -155,8 +155,8 @@ void nbt_ig_destroy_map(nbt_ig_map* map);        /* NULL is a no-op */
 /* Re-encodes an existing map in place from new probabilities of the same
  * dimensions (the map is rebuilt whenever a new point cloud has been fused,
  * Sec. III).  `prob` is a DEVICE pointer; the call is asynchronous on
- * `stream` and does not synchronise (one launch, or two for a map with
- * codes).  Values outside [0,1] or NaN are
+ * `stream` and does not synchronise (one launch; for a map with codes two in
+ * every 16th call, which gathers its palette anew).  Values outside [0,1] or NaN are
  * encoded as Unknown and recorded; nbt_ig_map_check() synchronises `stream`
  * and returns NBT_IG_EINVAL if any update since the last check saw one.
  * Evaluations already enqueued on other streams must finish first. */

@@ -85,7 +85,8 @@ struct nbt_ig_map {
     nbt::DevMap dm{};
     uint32_t* enc = nullptr;
     size_t enc_bytes = 0;
-    void* codes = nullptr;          // the codes, then the palette and its flag; may be absent
+    void* codes = nullptr;          // the codes, then the palette, its flag and count; may be absent
+    uint32_t updates = 0;           // calls of nbt_ig_update_map; every kPaletteEvery-th starts the palette anew
     float voxel = 0.0f;
     float origin[3] = {0, 0, 0};
     nbt_ig_classify cls{0.5f, 0.5f};

@@ -78,7 +78,7 @@ struct DevMap {
     float inv_s;            // 1/voxel_size (binary32)
     float ox, oy, oz;       // origin
     const uint8_t* codes;   // nullptr: the map has none
-    const uint32_t* palette;    // kCodes words, then the overflow flag
+    const uint32_t* palette;    // kCodes words, then the overflow flag and the count of words
     uint32_t code_bytes;    // size of codes in bytes
     uint32_t mx, my, mz;    // offset bits of each axis
     int csy, csz;           // lowest offset bit of Y >> 3 and of Z >> 3
@@ -178,9 +178,11 @@ struct TrajSplit {
 
 // ---- launchers (each defined next to its kernels) ----
 
-// Writes m's words (enc) and, when it has them, its codes and palette.
+// Writes m's words (enc) and, when it has them, its codes.  A new map's palette is
+// started from a sample of the grid, later ones are kept or started again.
+enum class PaletteStart { kept, first, again };
 hipError_t launch_encode_map(const float* prob, uint32_t* enc, const DevMap& m, float occ_thr,
-                             float free_thr, unsigned int* bad_flag, hipStream_t s);
+                             float free_thr, unsigned int* bad_flag, PaletteStart start, hipStream_t s);
 // Copies an encoded map into another storage order (dst laid out as dstm).
 hipError_t launch_relayout(const DevMap& src, uint32_t* dst, const DevMap& dstm, hipStream_t s);
 

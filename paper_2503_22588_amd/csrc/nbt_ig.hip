@@ -215,6 +215,8 @@ uint64_t set_layout_geometry(DevMap& dm, int layout) {
 // The fields of X and Y span powers of two, so a map takes up to 4 bytes of
 // codes per voxel, 69 MB for 256^3.
 constexpr size_t kCodesFrom = 4u << 20;
+// Updates of a map after which its palette is started anew from a sample.
+constexpr uint32_t kPaletteEvery = 16;
 static uint64_t set_code_geometry(DevMap& dm) {
     auto bits = [](int n) {
         int b = 3;
@@ -409,7 +411,7 @@ int nbt_ig_create_map(nbt_ig_ctx* ctx, const float* prob, int nx, int ny, int nz
     // its encoding takes 3 us without and 9 with them.
     const uint64_t bytes = set_code_geometry(dm);
     if (bytes && map->enc_bytes > kCodesFrom) {
-        if (hipMalloc(&map->codes, bytes + (kCodes + 1) * 4) == hipSuccess) {
+        if (hipMalloc(&map->codes, bytes + (kCodes + 2) * 4) == hipSuccess) {
             dm.codes = static_cast<const uint8_t*>(map->codes);
             dm.palette = reinterpret_cast<const uint32_t*>(dm.codes + bytes);
             dm.code_bytes = (uint32_t)bytes;
@@ -442,7 +444,7 @@ int nbt_ig_create_map(nbt_ig_ctx* ctx, const float* prob, int nx, int ny, int nz
     if (e != hipSuccess) { rc = hip_fail(e, "hipMalloc(flag)"); goto done; }
     e = hipMemsetAsync(map->bad, 0, sizeof(unsigned int), s);
     if (e != hipSuccess) { rc = hip_fail(e, "hipMemsetAsync(flag)"); goto done; }
-    e = launch_encode_map(src, map->enc, dm, c.occ_threshold, c.free_threshold, map->bad, s);
+    e = launch_encode_map(src, map->enc, dm, c.occ_threshold, c.free_threshold, map->bad, PaletteStart::first, s);
     if (e != hipSuccess) { rc = hip_fail(e, "map encoding"); goto done; }
     e = hipMemcpyAsync(&bad, map->bad, sizeof bad, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -479,8 +481,9 @@ int nbt_ig_update_map(nbt_ig_map* map, const float* prob, void* stream) {
     if (!prob) return fail(NBT_IG_EINVAL, "prob is NULL");
     DeviceGuard g(map->ctx->device);
     if (!g.ok) return fail(NBT_IG_EDEVICE, "cannot select device %d", map->ctx->device);
+    const PaletteStart start = ++map->updates % kPaletteEvery == 0 ? PaletteStart::again : PaletteStart::kept;
     hipError_t e = launch_encode_map(prob, map->enc, map->dm, map->cls.occ_threshold,
-                                     map->cls.free_threshold, map->bad, (hipStream_t)stream);
+                                     map->cls.free_threshold, map->bad, start, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "map encoding");
     return NBT_IG_OK;
 }
