@@ -168,8 +168,8 @@ struct TrajAccum {
 
 // How a call of T trajectories is split; groups == 1: one workgroup each.
 struct TrajSplit {
-    uint32_t trajectories;
     uint32_t groups;         // workgroups that share one trajectory's rays
+    uint32_t leading;        // workgroups before them that take the boxes beyond cap_words, or 0
     uint32_t parts;          // workgroups that sum up its bitset
     uint32_t cap_words;      // bitset words per trajectory; a larger box is left to one workgroup
     uint32_t* bits;

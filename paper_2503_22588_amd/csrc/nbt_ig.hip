@@ -152,7 +152,7 @@ static bool ensure_traj_scratch(nbt_ig_ctx* ctx, hipStream_t s) {
 // 13.2).  Unsplit and split: 16 x 12 poses 3.5 ms and 0.20, 64 x 12 3.6 and
 // 0.57, 200 x 24 7.1 and 2.85, 1000 x 24 16.5 and 13.2.
 static TrajSplit plan_traj_split(nbt_ig_ctx* ctx, uint32_t T, uint64_t tiles, hipStream_t s) {
-    TrajSplit sp{T, 1, 1, 0, nullptr, nullptr};
+    TrajSplit sp{1, 0, 1, 0, nullptr, nullptr};
     const uint64_t waves = (uint64_t)ctx->traj_waves, cu = (uint64_t)ctx->cu_count;
     if (T > kTrajSplitMost) return sp;
     const uint64_t per_wave = std::min<uint64_t>(std::max<uint64_t>(T * tiles / (48u * cu), 2u), 16u);
@@ -160,6 +160,7 @@ static TrajSplit plan_traj_split(nbt_ig_ctx* ctx, uint32_t T, uint64_t tiles, hi
     if (groups < 2 || (uint64_t)T * (groups + 1u) * waves * 64u >= (1ull << 32)) return sp;
     if (!ensure_traj_scratch(ctx, s)) return sp;
     sp.groups = groups;
+    sp.leading = T <= 4u * cu ? T : 0u;
     sp.parts = (uint32_t)std::min<uint64_t>((4u * cu + T - 1) / T, (uint64_t)kTrajParts);
     sp.cap_words = kTrajSplitWords / T;
     sp.bits = ctx->traj_bits;

@@ -361,6 +361,9 @@ __global__ __launch_bounds__(256) void traj_box_kernel(DevMap m, CamParams c,
 // were groups apart, a multiple of 8 as often as not: on one XCD of eight.
 // 200 x 12 poses of 64x48 rays at 2 cm, most boxes larger: 24 ms unsplit, 77 so.
 // 300 x 4 poses at 1 cm: 60 ms unsplit, 109 so, 60 with the leading workgroups).
+// Calls of more trajectories than fit the chip at once spread them anyhow: there it
+// is one of the trajectory's own, another part for each (1407 x 20 poses of 61x52
+// rays without such boxes 5.81 ms led, 5.74 so).
 template <int WAVES, bool COUNT, bool TRACE, bool SPLIT>
 __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(8, 8))) void traj_union_kernel(
     DevMap m, CamParams c, const float* __restrict__ poses, uint32_t L,
@@ -368,13 +371,14 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(8, 8
     uint32_t* __restrict__ counts, unsigned long long* __restrict__ visits,
     nbt_ig_ray_digest* __restrict__ trace, TrajSplit split) {
     extern __shared__ uint32_t lds_bits[];
-    const bool front = !SPLIT || blockIdx.x < split.trajectories;
-    const uint32_t slot = front ? blockIdx.x : blockIdx.x - split.trajectories;
-    const uint32_t t = front ? slot : slot / split.groups;
+    const bool leads = !SPLIT || blockIdx.x < split.leading;
+    const uint32_t slot = leads ? blockIdx.x : blockIdx.x - split.leading;
+    const uint32_t t = leads ? slot : slot / split.groups;
+    const uint32_t part = leads ? 0u : slot - t * split.groups;
     const TrajBox b = boxes[t];
     const bool whole = !SPLIT || ((uint64_t)b.nbits + 31u) / 32u > split.cap_words;
-    if (whole != front) return;
-    const uint32_t part = front ? 0u : slot - t * split.groups;
+    const bool mine = leads ? whole : !whole || (split.leading == 0u && part == t % split.groups);
+    if (SPLIT && !mine) return;
     // the bitset follows the walk's all-ones word and holds the clamp bit
     uint32_t* bits = lds_bits + 1;
     const uint32_t tid = threadIdx.x;
@@ -656,7 +660,7 @@ static hipError_t launch_union(const DevMap& m, const CamParams& c, const float*
     static std::atomic<size_t> lds_set[64];
     hipError_t e = allow_dynamic_lds(k, lds, lds_set, 64);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((traj_union_kernel<WAVES, COUNT, TRACE, SPLIT>), dim3(SPLIT ? T * (split.groups + 1u) : T),
+    hipLaunchKernelGGL((traj_union_kernel<WAVES, COUNT, TRACE, SPLIT>), dim3(SPLIT ? split.leading + T * split.groups : T),
                        dim3(WAVES * 64), lds, s, m, c, poses, L, boxes, pass_words, ig_union, counts, visits, trace,
                        split);
     e = hipGetLastError();

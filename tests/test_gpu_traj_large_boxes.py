@@ -1,5 +1,6 @@
 """GPU parity of split union IG with boxes around a trajectory's share of the scratch (2^25 words
-over the call's trajectories): all above it or some, led by workgroups of their own, and boxes of
+over the call's trajectories): all above it or some, led by workgroups of their own (up to four
+trajectories a CU) or not, and boxes of
 several LDS passes below it, shared by workgroups, against the CPU oracle."""
 
 import numpy as np
@@ -12,8 +13,8 @@ from workloads.configs import Camera
 pytestmark = pytest.mark.gpu
 
 
-# shares of 2^25 / t words: 2.0, 3.6 and 67 M positions; the map has 2.9 M
-@pytest.mark.parametrize("t,waves", [(536, 4), (300, 4), (16, 8)])
+# shares of 2^25 / t words: 1.0, 2.0, 3.6 and 67 M positions; the map has 2.9 M
+@pytest.mark.parametrize("t,waves", [(1100, 4), (536, 4), (300, 4), (16, 8)])
 @pytest.mark.parametrize("layout", [0, 1], ids=["linear", "column4"])
 def test_boxes_around_the_share(t, waves, layout):
     import torch
