@@ -524,13 +524,18 @@ int nbt_ig_map_info(const nbt_ig_map* map, int* nx, int* ny, int* nz, float* vox
 // rays on a 256^3 table-top map 530 -> 501 us, 4096 of them 7.6 -> 7.26 ms,
 // 500 of 47x39 rays on a 320^3 map 331 -> 275 us.  The balanced shape stays where it
 // is faster: 64 of 160x120 rays 150 us (two tiles 174, one 200), 500 of 10x9
-// rays 43 (52), whose perspectives need no combining, and short rays (512 of
-// 64x48 rays of 45 voxels 74, single waves 76-83).
+// rays 43 (52), whose perspectives need no combining, short rays (512 of
+// 64x48 rays of 45 voxels 74, single waves 76-83), and cameras of up to 64
+// tiles that fill workgroups of four, while their rays stay below some 200 voxels: there
+// single waves gain up to 4 % by codes or lose as much (512 of 64x48 rays of 132 voxels 155 us,
+// four waves 147; on a 100^3 map 124 and 129), but a map walked by its words in linear
+// order loses the lines that neighbouring tiles share (437 and 386; spheres 715 and 663).
 static VpLaunch long_ray_launch(const DevMap& m, const CamParams& c, uint32_t n, const VpLaunch& L0) {
     const double len = std::sqrt((double)c.dh * c.dh + (double)c.dv * c.dv + (double)c.range * c.range) * m.inv_s;
     if (!(len >= 100.0) || std::max(m.nx, std::max(m.ny, m.nz)) < 100) return L0;
     const uint32_t tiles = vp_tiles(c, 3);
     if (tiles <= 8 || (tiles > 64 && (uint64_t)n * tiles < 40000)) return L0;
+    if (tiles <= 64 && tiles % 4u == 0u && len < 200.0) return L0;
     const VpLaunch L{1, 3, tiles > 64 ? 2 : 1, 0, 8};
     return (uint64_t)n * vp_groups(c, L) * 64 < (1ull << 32) ? L : L0;
 }
