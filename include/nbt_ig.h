@@ -404,8 +404,10 @@ int nbt_ig_batch_autotune(nbt_ig_batch* batch, const uint32_t* vp_offsets, const
 
 /* Chooses the storage order of the batch's maps (all alike): times the batch
  * in every storage order (linear and the three column tile sizes) at its
- * current launch shape, leaves the maps in the fastest one (*best_layout, HOST; mean ms per run in *best_ms) and updates the
- * batch.  Synchronises `stream`; no other work may use the maps meanwhile.
+ * current launch shape, leaves the maps in the fastest one (*best_layout, HOST;
+ * mean ms per run in *best_ms; the first map's order where a map has codes and
+ * no other gains more than 2 %) and updates the batch.  Synchronises `stream`;
+ * no other work may use the maps meanwhile.
  * NBT_IG_EINVAL when another batch holds one of the maps too. */
 int nbt_ig_batch_autotune_layout(nbt_ig_batch* batch, const uint32_t* vp_offsets, const float* poses,
                                  float* ig_out, uint64_t* steps_out, void* stream, int* best_layout,
@@ -423,8 +425,9 @@ int nbt_ig_autotune_trajectories(nbt_ig_map* map, const nbt_ig_camera* cam, cons
 
 /* As nbt_ig_autotune_viewpoints, and first the map's storage order: times
  * nbt_ig_eval_viewpoints in every order at the context's launch shape, keeps
- * the map in the fastest one (*best_layout, HOST; see nbt_ig_map_set_layout),
- * then searches the launch shape.  The map must not be held by a batch. */
+ * the map in the fastest one (*best_layout, HOST; see nbt_ig_map_set_layout; a
+ * map with codes changes its order only for more than 2 %), then searches the
+ * launch shape.  The map must not be held by a batch. */
 int nbt_ig_autotune_map(nbt_ig_map* map, const nbt_ig_camera* cam, const float* poses, uint32_t n,
                         float* ig_out, uint64_t* steps_out, void* stream, nbt_ig_launch* best,
                         int* best_layout, float* best_ms);

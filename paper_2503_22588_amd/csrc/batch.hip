@@ -117,12 +117,10 @@ nbt_ig_launch from_vp(const VpLaunch& v) {
 // The storage orders a layout autotuner tries (NBT_IG_LAYOUT_* are 0..3).
 constexpr int kLayouts = NBT_IG_LAYOUT_COLUMN8 + 1;
 
-int fastest_layout(const float* ms) {
-    int best = 0;
-    for (int l = 1; l < kLayouts; ++l)
-        if (ms[l] < ms[best]) best = l;
-    return best;
-}
+// The walk over codes is the same in every order, so a map with codes keeps the one
+// it has unless another is faster by more than timings of one order differ (0.6 % here): by noise it would
+// land in 2x2 columns, say, whose encoding takes 15 us longer (256^3), timed or not.
+constexpr float kCodedMargin = 0.02f;
 
 // Exhaustive search over the launch grid (4 x 3 x 4 x 3 = 144 shapes): every
 // shape is applied, run once untimed (warm-up, graph rebuild) and timed over
@@ -355,7 +353,7 @@ int nbt_ig_batch_autotune_layout(nbt_ig_batch* b, const uint32_t* vp_offsets, co
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc != NBT_IG_OK) return rc;
-    const int lay = fastest_layout(ms);
+    const int lay = pick_layout(ms, kLayouts, start, b->coded ? kCodedMargin : 0.0f);
     if (int r2 = apply(lay)) return r2;
     *best_layout = lay;
     *best_ms = ms[lay] / 3.0f;
@@ -456,7 +454,7 @@ int nbt_ig_autotune_map(nbt_ig_map* map, const nbt_ig_camera* cam, const float* 
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc != NBT_IG_OK) return rc;
-    const int lay = fastest_layout(ms);
+    const int lay = pick_layout(ms, kLayouts, start, map->dm.codes ? kCodedMargin : 0.0f);
     if (int r2 = nbt_ig_map_set_layout(map, lay, stream)) return r2;
     *best_layout = lay;
     return nbt_ig_autotune_viewpoints(map, cam, poses, n, ig_out, steps_out, stream, best, best_ms);

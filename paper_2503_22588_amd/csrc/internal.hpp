@@ -40,6 +40,14 @@ __host__ __device__ inline int layout_tile_log2(int layout) {
          : layout == NBT_IG_LAYOUT_COLUMN4 ? 2
          : layout == NBT_IG_LAYOUT_COLUMN8 ? 3 : 0;
 }
+// The storage order to keep of `count` timed ones: the fastest, but an order only
+// takes the place of the current one when it is faster by the share `margin`.
+inline int pick_layout(const float* ms, int count, int current, float margin) {
+    int best = current;
+    for (int l = 0; l < count; ++l)
+        if (ms[l] < ms[best] && ms[l] < ms[current] * (1.0f - margin)) best = l;
+    return best;
+}
 inline bool valid_layout(int layout) { return layout >= NBT_IG_LAYOUT_LINEAR && layout <= NBT_IG_LAYOUT_COLUMN8; }
 
 // A map also holds one byte per voxel, its code: the index of its word in a
