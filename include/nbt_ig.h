@@ -135,12 +135,16 @@ int nbt_ig_ctx_get_map_layout(const nbt_ig_ctx* ctx, int* layout);
  * in [0,1]; HOST or DEVICE pointer) into a device-resident encoded map: each
  * voxel stores its Eq. 2 gain with the sign bit marking Occupied, inside a
  * one-voxel border that stops every ray leaving the map, stored in the
- * context's map layout.  Beside words of more than 4 MiB the map holds a
- * one-byte code per word and the palette of the words those codes stand for
- * (a quarter of the words' memory again, not part of nbt_ig_map_info's
- * device_bytes); a map with more different words than codes, or without
- * memory for the codes, is walked by its words, with the same results.  1 <= n <= 4096 per axis and (nx+2)(ny+2)(nz+2) <
- * 2^30 (for the column orders: the count with x and y padded to whole tiles < 2^30).  `origin` (HOST, 3 floats) is the world
+ * context's map layout.  Beside words of more than 4 MiB the map holds one-byte
+ * codes of them and the palette of the words those codes stand for.  The codes
+ * are addressed by bit fields: nx+2 and ny+2 are padded to powers of two and
+ * nz+2 to a multiple of 8, so they take as much memory again as the words at
+ * worst (2.7 times as much on maps of few voxels on an axis;
+ * nbt_ig_map_code_bytes, not part of nbt_ig_map_info's device_bytes).  A map
+ * with more different words than some 220, or without memory for the codes, is
+ * walked by its words, with the same results.  1 <= n <= 4096 per axis and
+ * (nx+2)(ny+2)(nz+2) < 2^30 (for the column orders: the count with x and y
+ * padded to whole tiles < 2^30).  `origin` (HOST, 3 floats) is the world
  * position of the min corner of voxel (0,0,0); `voxel_size` > 0 is s_Vox.
  * `cls` may be NULL (0.5/0.5); 0 <= free_threshold <= occ_threshold <= 1.
  * Probabilities outside [0,1] or NaN give NBT_IG_EINVAL (checked on the
@@ -211,6 +215,10 @@ int nbt_ig_map_check(nbt_ig_map* map, void* stream);
 int nbt_ig_map_info(const nbt_ig_map* map, int* nx, int* ny, int* nz, float* voxel_size,
                     float origin[3], size_t* device_bytes);
 int nbt_ig_map_layout(const nbt_ig_map* map, int* layout);
+
+/* Device memory of a map's codes and their palette beside its device_bytes
+ * (*bytes, HOST); 0 for a map without codes. */
+int nbt_ig_map_code_bytes(const nbt_ig_map* map, size_t* bytes);
 
 /* Rewrites an existing map in another storage order (NBT_IG_LAYOUT_*): a new
  * device buffer is filled from the old one on `stream`, the call synchronises
@@ -339,10 +347,11 @@ int nbt_ig_trace_paths(const nbt_ig_map* map, const nbt_ig_camera* cam, const fl
  * order (C <= 65536); pipeline_depth in
  * {1,2,4,8} map gathers in flight per ray (0 = default, 8).  A new context
  * starts at 4 waves, 8x8 tiles, balanced tiles per wave, no remap, 8 gathers
- * in flight.  While that starting shape stands, a call chooses for itself where another is
- * faster: small calls walk each ray in segments on several lanes, calls of
- * long rays run single-wave workgroups of one or two tiles.  Any shape gives the same step counts; IG agrees to the
- * last-place rounding of its sum.
+ * in flight.  That starting shape stands for the library's choice, also when it
+ * is set again or an autotuner settles on it: small calls then walk each ray in
+ * segments on several lanes, calls of long rays may run single-wave workgroups
+ * of one or two tiles.  Every other shape is taken literally.  Any shape gives
+ * the same step counts; IG agrees to the last-place rounding of its sum.
  */
 typedef struct {
     int32_t waves_per_group;

@@ -85,6 +85,7 @@ _sig("nbt_ig_insert_scans", C.c_int, _vp, C.POINTER(CameraT), _vp, _vp, _u32, C.
 _sig("nbt_ig_map_check", C.c_int, _vp, _vp)
 _sig("nbt_ig_map_info", C.c_int, _vp, C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int),
      C.POINTER(C.c_float), C.POINTER(C.c_float), C.POINTER(C.c_size_t))
+_sig("nbt_ig_map_code_bytes", C.c_int, _vp, C.POINTER(C.c_size_t))
 _sig("nbt_ig_eval_viewpoints", C.c_int, _vp, C.POINTER(CameraT), _vp, _u32, _vp, _vp, _vp)
 _sig("nbt_ig_probe_sink_words", C.c_int, _vp)
 _sig("nbt_ig_probe_memory", C.c_int, _vp, C.c_int, _vp, C.c_size_t, _u32, _vp, _vp)
@@ -310,8 +311,10 @@ class Map:
                                     org, C.byref(nb)))
         lay = C.c_int()
         _check(_lib.nbt_ig_map_layout(self.handle, C.byref(lay)))
+        cb = C.c_size_t()
+        _check(_lib.nbt_ig_map_code_bytes(self.handle, C.byref(cb)))
         return {"dims": (nx.value, ny.value, nz.value), "voxel": vs.value, "origin": tuple(org),
-                "device_bytes": nb.value, "layout": lay.value}
+                "device_bytes": nb.value, "code_bytes": cb.value, "layout": lay.value}
 
     def close(self):
         if self.handle and self.ctx.handle:

@@ -67,6 +67,7 @@ inline bool valid_layout(int layout) { return layout >= NBT_IG_LAYOUT_LINEAR && 
 // face.
 constexpr uint32_t kCodes = 256;
 constexpr uint32_t kCodeFree = 0xFFFFFFFFu;
+constexpr uint32_t kPaletteWords = kCodes + 2;       // with the overflow flag and the count
 
 __host__ __device__ inline uint32_t code_offset(int sy, int sz, uint32_t X, uint32_t Y, uint32_t Z) {
     const uint32_t lo = (X & 3u) | (Y & 1u) << 2 | (Z & 1u) << 3 | (Y & 2u) << 3 | (Z & 2u) << 4 | (X & 4u) << 4 |
