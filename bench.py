@@ -28,7 +28,7 @@ if ROOT not in sys.path:
 
 METRIC = "viewpoint IG evals/s + voxel-steps/s vs L2/HBM roofline; surrogate vs raycast"
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E
-BYTES_PER_STEP = 4             # one encoded map word gathered per visited voxel
+BYTES_PER_WORD, BYTES_PER_CODE = 4, 1   # gathered per visited voxel, by the map's words or its codes
 BYTES_PER_VIEWPOINT = 48 + 4 + 8   # pose in, IG and step count out
 
 
@@ -48,8 +48,8 @@ FINGERPRINT_FILES = (
     "workloads/poses.py",
 )
 # what the rooflines of the per-perspective walks count as algorithmic bytes
-WORD_BYTES_NOTE = ("4 B per voxel step, one encoded word; where a map's words exceed 4 MiB the walk gathers "
-                   "their 1-B codes, a quarter of these bytes")
+STEP_BYTES_NOTE = ("bytes gathered per voxel step: 1 (a code) in maps with codes walked 8 gathers deep, "
+                   "4 (an encoded word) in the others")
 COUNTERS_PROFILE = "profiles/ig_viewpoints_cfg2_counters.md"
 
 
@@ -65,6 +65,21 @@ def kernel_fingerprint():
         with open(os.path.join(ROOT, rel), "rb") as f:
             h.update(rel.encode() + b"\0" + f.read() + b"\0")
     return h.hexdigest()[:16]
+
+
+def step_bytes(info, depth):
+    """Bytes a per-perspective walk gathers per voxel step of a map (its info()): its codes where
+    it has them and the walk is the one that reads them.  The scenes here have three words, so
+    their palettes never overflow."""
+    return BYTES_PER_CODE if info["code_bytes"] and depth == 8 else BYTES_PER_WORD
+
+
+def step_set(info, depth):
+    """Bytes of a map that such a walk gathers from: the codes of its voxels and border, or its words."""
+    if step_bytes(info, depth) == BYTES_PER_WORD:
+        return int(info["device_bytes"])
+    nx, ny, nz = info["dims"]
+    return (nx + 2) * (ny + 2) * (nz + 2) * BYTES_PER_CODE
 
 
 def launch_key(layout, launch):
@@ -251,7 +266,7 @@ def measure_ceilings(nbt, ctx, reps=10):
     return out
 
 
-def level_fractions(steps_per_s, map_bytes, ceilings):
+def level_fractions(steps_per_s, map_bytes, ceilings, per_step=BYTES_PER_WORD):
     """The walk's voxel-step rate (one 4-byte word per step) against the probes' rates at the
     working set closest to the map's size."""
     if not ceilings:
@@ -260,7 +275,7 @@ def level_fractions(steps_per_s, map_bytes, ceilings):
     c = ceilings[label]
     level = {"1MiB": "L2", "64MiB": "Infinity Cache (MALL)", "1GiB": "HBM"}[label]
     return {"map_bytes": map_bytes, "level": level, "ceiling_working_set": label,
-            "frac_vs_stream": 4 * steps_per_s / (c["stream_gbs"] * 1e9),
+            "frac_vs_stream": per_step * steps_per_s / (c["stream_gbs"] * 1e9),
             "frac_vs_quad_gather": steps_per_s / c["quad_gather_words_per_s"],
             "frac_vs_gather": steps_per_s / c["gather_words_per_s"]}
 
@@ -284,13 +299,13 @@ def measure_mfma_ceiling(nbt, ctx, reps=5, iters=2048):
     return out
 
 
-def roofline_of(kernel, steps_per_s, map_bytes, ceilings):
-    """The contract's roofline object for a walk kernel: algorithmic bytes (4 per voxel step)
+def roofline_of(kernel, steps_per_s, map_bytes, ceilings, per_step=BYTES_PER_WORD):
+    """The contract's roofline object for a walk kernel: algorithmic bytes (per_step per voxel step)
     against the HBM peak, plus the fractions of the measured ceilings of the map's level."""
-    ach = 4 * steps_per_s / 1e9
+    ach = per_step * steps_per_s / 1e9
     return {"kernel": kernel, "bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": ach / HBM_PEAK_GBS, "traffic": None,
-            "levels": level_fractions(steps_per_s, map_bytes, ceilings)}
+            "levels": level_fractions(steps_per_s, map_bytes, ceilings, per_step)}
 
 
 def extra_trajectories(nbt, ctx, reps, ceilings=None):
@@ -390,16 +405,21 @@ def extra_batch(nbt, ctx, reps, ceilings=None):
     layout, _ = b.autotune_layout(offsets, allp, ig, st)     # untimed set-up: map order, then shape
     best, _ = b.autotune(offsets, allp, ig, st)
     ms = _timed(lambda: b.run(offsets, allp, ig, st), reps, torch.cuda.current_stream())
-    steps = int(st.cpu().numpy().view(np.uint64).sum())
+    per = st.cpu().numpy().view(np.uint64)
+    steps = int(per.sum())
+    infos, depth = [mm.info() for mm in maps], b.get_launch()["pipeline_depth"]
+    gathered = sum(int(part.sum()) * step_bytes(i, depth)
+                   for i, part in zip(infos, np.split(per, np.cumsum(counts)[:-1])))
     rays = n * w.camera.width * w.camera.height
     res = {"workload": f"64 maps (sizes in {{64,96,128,192,256}}^3, 5 cm), {n} perspectives, 64x48 rays",
            "batch_latency_ms": ms, "viewpoint_evals_per_s": n / (ms * 1e-3), "rays_per_s": rays / (ms * 1e-3),
            "voxel_steps_per_s": steps / (ms * 1e-3), "launch": b.get_launch(),
            "map_layout": nbt.LAYOUT_NAMES[layout],
            "untuned": untuned, "tuner_speedup": untuned["batch_latency_ms"] / ms,
-           "roofline": roofline_of("ig_batch_kernel", steps / (ms * 1e-3),
-                                   sum(int(mm.info()["device_bytes"]) for mm in maps), ceilings)}
-    res["roofline"]["algorithmic_note"] = WORD_BYTES_NOTE
+           "roofline": roofline_of("ig_batch_kernel", steps / (ms * 1e-3), sum(step_set(i, depth) for i in infos),
+                                   ceilings, gathered / steps)}
+    res["roofline"]["algorithmic_note"] = STEP_BYTES_NOTE
+    res["roofline"]["bytes_per_step"] = gathered / steps
     b.close()
     return res
 
@@ -727,7 +747,9 @@ def main():
     evals_per_s = n * args.steps / wall
     rays = n * cam.width * cam.height
 
-    alg_bytes = BYTES_PER_STEP * total_steps + BYTES_PER_VIEWPOINT * n
+    info, depth = m.info(), ctx.get_launch()["pipeline_depth"]
+    per_step = step_bytes(info, depth)
+    alg_bytes = per_step * total_steps + BYTES_PER_VIEWPOINT * n
     achieved_gbs = alg_bytes / (ray_ms * 1e-3) / 1e9
     result = {
         "metric": METRIC,
@@ -768,7 +790,8 @@ def main():
             "frac": achieved_gbs / HBM_PEAK_GBS,
             "traffic": None,
             "algorithmic_gb_per_launch": alg_bytes / 1e9,
-            "algorithmic_note": WORD_BYTES_NOTE,
+            "bytes_per_step": per_step,
+            "algorithmic_note": STEP_BYTES_NOTE,
         },
     }
     shape = launch_key(nbt.LAYOUT_NAMES[m.info()["layout"]], ctx.get_launch())
@@ -792,8 +815,8 @@ def main():
         result["roofline"]["traffic_note"] = (f"no committed counters for these sources and this map order and "
                                               f"launch shape ({shape})")
     if ceilings:
-        result["roofline"]["levels"] = level_fractions(total_steps / (ray_ms * 1e-3), int(m.info()["device_bytes"]),
-                                                       ceilings)
+        result["roofline"]["levels"] = level_fractions(total_steps / (ray_ms * 1e-3), step_set(info, depth), ceilings,
+                                                       per_step)
         result["memory_ceilings"] = ceilings
     if not args.no_extras:
         cx = nbt.Context(0)            # default settings, untouched by the main line's tuning
