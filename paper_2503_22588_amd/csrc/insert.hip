@@ -67,10 +67,10 @@ __global__ __launch_bounds__(256) void insert_mark_kernel(DevMap m, CamParams c,
 }
 
 // One thread per 8 voxels (16 bytes of marks, 32 of values).  PROB: also the
-// probability of every voxel.  vec: all three arrays are 16-byte aligned.
+// probability of every voxel (P may be L: a voxel's probability is stored after its
+// log-odds).  vec: all three arrays are 16-byte aligned.
 template <bool PROB>
-__global__ __launch_bounds__(256) void insert_apply_kernel(uint32_t* __restrict__ marks,
-                                                           float* __restrict__ L, float* __restrict__ P,
+__global__ __launch_bounds__(256) void insert_apply_kernel(uint32_t* __restrict__ marks, float* L, float* P,
                                                            uint64_t nvox, nbt_ig_insert_params p, bool vec) {
     const uint64_t v0 = 8 * ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x);
     if (v0 >= nvox) return;
