@@ -135,8 +135,8 @@ int nbt_ig_ctx_get_map_layout(const nbt_ig_ctx* ctx, int* layout);
  * in [0,1]; HOST or DEVICE pointer) into a device-resident encoded map: each
  * voxel stores its Eq. 2 gain with the sign bit marking Occupied, inside a
  * one-voxel border that stops every ray leaving the map, stored in the
- * context's map layout.  Beside words of more than 4 MiB the map holds one-byte
- * codes of them and the palette of the words those codes stand for.  The codes
+ * context's map layout.  Beside words of more than 4 MiB (6 voxels in x or
+ * more) the map holds one-byte codes of them and the palette of the words those codes stand for.  The codes
  * are addressed by bit fields: nx+2 and ny+2 are padded to powers of two and
  * nz+2 to a multiple of 8, so they take as much memory again as the words at
  * worst (2.7 times as much on maps of few voxels on an axis;

@@ -271,7 +271,7 @@ __device__ __forceinline__ void word_coords(const DevMap& m, uint32_t idx, uint3
 // word spent most of its time on four divisions per word: 50 us for 256^3 in
 // 4x4 columns, 30 now; 47 and 31 in linear order; with the codes 35 and 38).
 // How many lanes lie along x depends on the map (lanes_along; with always 64 words to a
-// row, 1 x 4000 x 4000 took 1490 us in linear order, now 215 with codes and 85 without).
+// row, 1 x 4000 x 4000 took 1490 us in linear order, 85 now).
 //
 // Every thread steps through LAYERS layers, their loads in flight together: 4,
 // or 1 for a map without codes that is too small to fill the chip so (64^3 in
@@ -486,8 +486,8 @@ static void launch_encode_column(const float* prob, uint32_t* enc, const DevMap&
                                  unsigned int* bad_flag, hipStream_t s) {
     constexpr int T = 1 << TL, kWide = TL == 1 ? 2 : 4, kHigh = TL == 1 ? 2 : 1;
     const uint32_t along = (uint32_t)(m.nbx * (T / kWide)), rows = (uint32_t)(m.nby * (T / kHigh));
-    // a wave's region is at least 8 voxels in x and 4 in y: whole lines of codes
-    const int xl = lanes_along(along, TL == 1 ? 2 : 1, TL == 1 ? 6 : TL == 2 ? 4 : 3);
+    // with codes a wave's region is at least a line of them wide
+    const int xl = lanes_along(along, !m.codes ? 0 : TL == 1 ? 2 : 1, TL == 1 ? 6 : TL == 2 ? 4 : 3);
     const unsigned gx = (along + (1u << xl) - 1u) >> xl, pz = (unsigned)m.pz;
     auto go = [&](auto kernel, unsigned layers) {
         // the four waves take layers above one another, or rows where there are too few layers
@@ -504,7 +504,7 @@ static void launch_encode_column(const float* prob, uint32_t* enc, const DevMap&
 
 static void launch_encode_linear(const float* prob, uint32_t* enc, const DevMap& m, float occ_thr, float free_thr,
                                  unsigned int* bad_flag, hipStream_t s) {
-    const int xl = lanes_along((uint32_t)m.px, m.codes ? 3 : 2, 6);
+    const int xl = lanes_along((uint32_t)m.px, m.codes ? 3 : 0, 6);
     const unsigned gx = ((unsigned)m.px + (1u << xl) - 1u) >> xl, pz = (unsigned)m.pz;
     const unsigned rows = 256u >> xl, gy = ((unsigned)m.py + rows - 1u) / rows, gz = (pz + kEncodeLayers - 1) / kEncodeLayers;
     auto go = [&](auto kernel, unsigned z) {

@@ -7,7 +7,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("shape,coded", [((64, 64, 64), False), ((100, 100, 100), True), ((256, 256, 256), True),
-                                         ((320, 320, 320), True), ((254, 254, 200), True), ((2000, 1500, 1), True),
+                                         ((320, 320, 320), True), ((254, 254, 200), True), ((2000, 1500, 1), True), ((5, 1500, 1000), False),
+                                         ((6, 1500, 1000), True),
                                          ((1022, 1, 4000), True)],
                          ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else "")
 def test_memory_of_words_and_codes(shape, coded):
