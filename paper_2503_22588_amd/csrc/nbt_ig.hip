@@ -217,7 +217,9 @@ uint64_t set_layout_geometry(DevMap& dm, int layout) {
 // 8: 69.2 MB beside 68.7 of words for 256^3 (258 -> 512 twice), 1.07 times the words at
 // worst where every axis has 100 voxels or more, 2.7 times for 4095 x 4095 x 1.
 constexpr size_t kCodesFrom = 4u << 20;
-// Updates of a map after which its palette is started anew from a sample.
+// Updates of a map after which its palette is started anew from a sample: in every
+// one it cost 7 us (17 on a map of many words), never would keep words no longer
+// met and an overflow for good.
 constexpr uint32_t kPaletteEvery = 16;
 static uint64_t set_code_geometry(DevMap& dm) {
     auto bits = [](int n) {
@@ -409,8 +411,8 @@ int nbt_ig_create_map(nbt_ig_ctx* ctx, const float* prob, int nx, int ny, int nz
     dm.ox = origin[0]; dm.oy = origin[1]; dm.oz = origin[2];
     // The codes; a map that cannot have them is walked by its words, and so is
     // one whose words fit an XCD's L2 anyway: its evaluations gain nothing
-    // (32 perspectives of 64x48 rays in a 64^3 map: 16 us by words, 17 by codes) and
-    // its encoding takes 3 us without and 9 with them.
+    // (32 perspectives of 64x48 rays in a 64^3 map: 16 us by words, 17 by codes;
+    // 500 of 47x39 rays in a 104^3 map, 5 MB, 141 and 100).
     // So is one of fewer than 8 padded voxels in x, whose lines of codes are mostly padding
     // (encoding 1 x 4000 x 4000 in linear order 203 us with codes, 85 without).
     const uint64_t bytes = dm.px >= 8 ? set_code_geometry(dm) : 0;

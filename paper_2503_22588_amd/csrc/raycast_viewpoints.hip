@@ -614,7 +614,8 @@ hipError_t launch_eval_viewpoints(const DevMap& m, const CamParams& c, const flo
 // and 69.  Short rays do not pay either: 8 x 3072 rays of up to 80 voxels 15
 // and 15.5.
 // A workgroup of one wave spreads best; it grows to four while a perspective
-// would have more than 8 of them (their combine is serial: 35 ns each) or
+// would have more than 8 of them (one perspective's combine in turn, 35 ns each; 256
+// perspectives at once 3 ns a workgroup, 4096 less than 1) or
 // the call more than two per CU.
 constexpr uint64_t kSegMaxRays = 32768, kSegLanes = 49152;
 constexpr uint32_t kSegVoxels = 24;
