@@ -36,9 +36,10 @@ __device__ __forceinline__ uint32_t encode_prob(float p, float occ_thr, float fr
 // entry holds the lower 21, its distance from that place and the code, so it
 // names the whole word, and one read and one comparison give the code.  With
 // 224 words some 10 % lie one place on and 1 % further; words that crowd so
-// that one finds no room within 8 places count as too many.  (Looked up by
-// probing a copy of the palette, with the sampling pass in every encoding, 150 words
-// scattered over 320^3 took 296 us and three 104, now 83 and 82.)
+// that one finds no room within 7 places count as too many.  (At an eighth place a free
+// entry, all ones, would pass for that of a word whose lower 21 bits are all ones.)
+// Looked up by probing a copy of the palette, with the sampling pass in every encoding,
+// 150 words scattered over 320^3 took 296 us and three 104, now 83 and 82.
 //
 // New words: thousands of workgroups meet them at once, and swaps of one address
 // take 15 ns each.  So a workgroup gathers the words it lacks, a thread looks after each, and
@@ -48,7 +49,7 @@ __device__ __forceinline__ uint32_t encode_prob(float p, float occ_thr, float fr
 // 125 in 16 of them: 57 us an encoding, 80 with eight looks.
 constexpr uint32_t kCodeProbes = 24;             // palette slots tried for a new word
 constexpr uint32_t kCodeMost = 224;
-constexpr uint32_t kTableBits = 11, kTableSize = 1u << kTableBits, kTableFar = kTableSize >> 8;
+constexpr uint32_t kTableBits = 11, kTableSize = 1u << kTableBits, kTableFar = (kTableSize >> 8) - 1u;
 constexpr uint32_t kSetSize = 256;
 
 struct CodeTable {

@@ -111,3 +111,30 @@ def test_replayed_updates(nbt):
         assert torch.equal(got, again)
         _check(nbt, m, cam, poses, k)
     ctx.close()
+
+
+def test_words_of_edge_hashes(nbt):
+    """Words whose hash (times 0x9E3779B1) has lower 21 bits all ones or all zero, new in an update."""
+    import torch
+    from workloads.configs import Camera
+    inv = pow(0x9E3779B1, -1, 2 ** 32)
+    free, occupied = [], []
+    for low in (0x1FFFFF, 0):
+        w = np.array([inv * (h << 21 | low) % 2 ** 32 for h in range(2048)], np.uint32)
+        gain = (w & np.uint32(0x7FFFFFFF)).view(np.float32)
+        free += [p for p in gain[w < 2 ** 31] if 1e-3 < p < 0.5]
+        occupied += [np.float32(1) - g for g in gain[w >= 2 ** 31] if 0.0 < g < 1.0 and
+                     np.float32(1) - (np.float32(1) - g) == g and np.float32(1) - g > 0.15]
+    assert len(free) >= 12 and len(occupied) >= 3
+    shape, voxel = (118, 103, 97), 0.05
+    cam, poses = Camera(70, 50, 90.0, 80.0, 6.0), _poses(shape, voxel, 8, 3)
+    ctx = nbt.Context(0)
+    for p, classify in [(p, (0.5, 0.5)) for p in free] + [(p, (0.15, 0.15)) for p in occupied]:
+        print(f"[gpu] word of {p}, classified by {classify}", flush=True)
+        P = torch.full(shape[::-1], 0.125, device="cuda")
+        m = nbt.Map(ctx, P, voxel, (0.0, 0.0, 0.0), classify)
+        assert m.info()["code_bytes"] > 0
+        P[::9, ::7, ::5] = float(p)
+        m.update(P)
+        _check(nbt, m, cam, poses, p)
+    ctx.close()
