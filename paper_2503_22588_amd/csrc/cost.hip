@@ -19,19 +19,12 @@
 // state over all perspectives (20 workgroups of 4 waves on the chip) and 5 us
 // for the horizons' sum in a launch of its own; 29 us in this kernel, 17 in
 // the one below.  1024 horizons: 55 us here, 58 there; 4096: 131 and 203.
-#include <algorithm>
-
 #include "internal.hpp"
 
 namespace nbt {
 
-constexpr int kCostWaves = 16;
 constexpr int kCostRun = 64;     // pairs summed in binary32 before they join the binary64 sum
 constexpr int kCostBlock = 8;    // perspectives whose scalar loads are in flight together
-
-// States of one workgroup: whole horizons where one fits 64 lanes (the
-// workgroup then also sums their cost), else 64 states.
-static uint32_t cost_tile(uint32_t steps) { return steps <= 64 ? 64 / steps * steps : 64; }
 
 // The outputs of the states one wave holds (lane's: q), and with `cost` those of the
 // `horizons` whole horizons they are: every horizon's terms are summed in order.
@@ -324,21 +317,6 @@ __global__ __launch_bounds__(256) void horizon_cost_kernel(const float* __restri
 // longer (256 x 1: 9.7 and 7.2; 64 x 16 perspectives 82 and 11).
 static bool horizon_alone(uint32_t h, uint32_t k, uint32_t nb, uint32_t np, int cu_count) {
     return k <= 32 && 2u * h <= 3u * (uint32_t)cu_count && np >= 128 && (uint64_t)nb * np >= 1000;
-}
-
-// Waves that split a tile's perspectives: 10 perspectives each at least, and
-// no more than the chip holds at once (24 a CU), since every workgroup pays
-// for its barriers and the sums' way through LDS.  16 waves for all: 1e6 x 1
-// states against 1 x 10 128 us, one wave 16; 30,000 x 20 against 1 x 100 150, two 30; 10,000 x 100
-// against 10 x 500 1557, two 1138.  In a large call one wave alone is slower
-// with many perspectives (1223 there), two are within 5 % of the best.
-static int query_waves(uint32_t tiles, uint32_t nb, uint32_t np, int cu_count) {
-    const uint64_t pairs = (uint64_t)nb * np, cu = (uint64_t)cu_count;
-    const uint64_t least = tiles >= 32u * cu ? 2u : 4u;
-    const uint64_t most = std::min(pairs / 10u, std::max(24u * cu / tiles, least));
-    int w = kCostWaves;
-    while (w > 1 && (uint64_t)w > most) w /= 2;
-    return w;
 }
 
 hipError_t launch_eval_cost(const float* id_pos, const float* id_ig, uint32_t nb, uint32_t np, float p,

@@ -1,6 +1,7 @@
 // internal.hpp -- types shared by the library's translation units (not installed).
 #pragma once
 
+#include <algorithm>
 #include <atomic>
 
 #include <hip/hip_runtime.h>
@@ -49,6 +50,27 @@ inline int pick_layout(const float* ms, int count, int current, float margin) {
     return best;
 }
 inline bool valid_layout(int layout) { return layout >= NBT_IG_LAYOUT_LINEAR && layout <= NBT_IG_LAYOUT_COLUMN8; }
+
+constexpr int kCostWaves = 16;
+// States of one workgroup of the planner's cost terms: whole horizons where one
+// fits 64 lanes (the workgroup then also sums their cost), else 64 states.
+inline uint32_t cost_tile(uint32_t steps) { return steps <= 64 ? 64 / steps * steps : 64; }
+// Waves that split a tile's perspectives: 10 perspectives each at least, and
+// no more than the chip holds at once (24 a CU), since every workgroup pays
+// for its barriers and the sums' way through LDS.  16 waves for all: 1e6 x 1
+// states against 1 x 10 128 us, one wave 16; 30,000 x 20 against 1 x 100 150, two 30; 10,000 x 100
+// against 10 x 500 1557, two 1138.  In a large call one wave alone is slower
+// with many perspectives (1223 there), two are within 5 % of the best.  A
+// launch has less than 2^32 threads: 1.1e9 states in horizons of 33 are done
+// by one wave a tile.
+inline int query_waves(uint32_t tiles, uint32_t nb, uint32_t np, int cu_count) {
+    const uint64_t pairs = (uint64_t)nb * np, cu = (uint64_t)cu_count;
+    const uint64_t least = tiles >= 32u * cu ? 2u : 4u;
+    const uint64_t most = std::min(pairs / 10u, std::max(24u * cu / tiles, least));
+    int w = kCostWaves;
+    while (w > 1 && ((uint64_t)w > most || (uint64_t)tiles * (uint64_t)w * 64u >= (1ull << 32))) w /= 2;
+    return w;
+}
 
 // A map also holds one byte per voxel, its code: the index of its word in a
 // palette of the map's distinct words (kCodes entries; 0 is the sentinel, 1

@@ -1,5 +1,5 @@
 """Rules of the library's host side, from a CPU build of its headers: which storage order an
-autotuner keeps of those it timed."""
+autotuner keeps of those it timed, and the threads of the planner's cost terms."""
 
 import ctypes as C
 import importlib.util
@@ -38,3 +38,13 @@ def rules(tmp_path_factory):
 def test_order_kept(rules, ms, current, margin, kept):
     a = np.array(ms, np.float32)
     assert rules.pick_layout(a.ctypes.data_as(C.c_void_p), 4, current, C.c_float(margin)) == kept
+
+
+@pytest.mark.parametrize("nb,np_", [(1, 1), (1, 10), (2, 10), (10, 500), (1000, 1000)])
+def test_cost_threads(rules, nb, np_):
+    """A launch has less than 2^32 threads, up to the most states a call accepts (below 2^31)."""
+    rules.cost_threads.restype = C.c_ulonglong
+    for steps in [*range(1, 67), 100, 1000]:
+        for states in (steps, 10 ** 6 // steps * steps, (2 ** 31 - 1) // steps * steps, 2 ** 30 // steps * steps):
+            threads = rules.cost_threads(C.c_uint32(states), C.c_uint32(steps), C.c_uint32(nb), C.c_uint32(np_), 256)
+            assert states <= threads < 2 ** 32, (states, steps)
