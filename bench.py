@@ -267,8 +267,8 @@ def measure_ceilings(nbt, ctx, reps=10):
 
 
 def level_fractions(steps_per_s, map_bytes, ceilings, per_step=BYTES_PER_WORD):
-    """The walk's voxel-step rate (one 4-byte word per step) against the probes' rates at the
-    working set closest to the map's size."""
+    """The walk's voxel-step rate (one gather of per_step bytes each) against the probes' rates at the
+    working set closest to what it gathers from (map_bytes)."""
     if not ceilings:
         return None
     label = "1MiB" if map_bytes <= (4 << 20) else ("64MiB" if map_bytes <= (192 << 20) else "1GiB")
